@@ -1,12 +1,12 @@
 // Batched entry points: many independent (H, S) systems of uneven size in one set of launches.
 //
-// Every CG stage is one launch over all systems. The products are grouped persistent GEMMs that
-// walk the concatenated tile lists of all systems (FP32 or FP64 MFMA, a system that has stopped
+// Every CG stage is one launch over all systems. The products are grouped GEMMs over the
+// concatenated tile lists of all systems (FP32 or FP64 MFMA, a system that has stopped
 // is skipped through its device flag); the reductions, the line minimum and the updates are
-// grouped kernels with one y-slice per system (FP64 accumulation). The first line search of a
-// phase runs eagerly and autotunes the macro tile of each grouped product; then two line
-// searches are captured in a hipGraph and the graph is replayed until every system has
-// stopped. Setup (shift, preconditioner inverse, FP32 copies) is per system.
+// grouped kernels with one y-slice per system (FP64 accumulation). The tile of each grouped
+// product follows from the sizes (direct_choose). The first line search of a phase runs eagerly;
+// then two line searches are captured in a hipGraph and the graph is replayed until every system
+// has stopped. Setup (shift, preconditioner inverse, FP32 copies) is per system.
 //
 // Precision: an FP32 phase (FP32 products and state), an FP64 phase, or the FP32 phase to the
 // looser tolerance omm_batch_set_mixed_tol() followed by an FP64 phase from its C to `tol`
@@ -55,8 +55,7 @@ struct OpList {
   int* d_tiles = nullptr;
   const int** d_done = nullptr;
   int cap = 0;
-  int grid = 0;
-  bool tuned = false;
+  std::vector<int> tile_start;  // tile prefix sums (host copy, kept until the upload has run)
 };
 
 }  // namespace
@@ -248,8 +247,8 @@ GemmOp gop(int M, int N, int K, const void* A, int64_t lda, const void* B, int64
   return op;
 }
 
-// Tile prefix sums for `tile`, uploaded with the op list; grid = min(tiles, 2 per CU).
-int upload_list(omm_batch* b, OpList& L, int tile) {
+// Picks the tile, uploads the op list and its tile prefix sums.
+int upload_list(omm_batch* b, OpList& L) {
   const int n = (int)L.ops.size();
   if (n == 0) return OMM_OK;
   if (L.cap < n) {
@@ -260,54 +259,24 @@ int upload_list(omm_batch* b, OpList& L, int tile) {
       return bfail(b, OMM_E_ALLOC, "hipMalloc failed");
     L.cap = n;
   }
-  std::vector<int> ts(n + 1, 0);
-  const int bm = gemm_tile_rows(tile, L.d.compute), bn = gemm_tile_cols(tile, L.d.compute);
+  direct_choose(L.d, L.ops.data(), n);
+  L.tile_start.assign(n + 1, 0);
+  const int bm = gemm_tile_rows(L.d.tile, L.d.compute), bn = gemm_tile_cols(L.d.tile, L.d.compute);
   for (int i = 0; i < n; ++i)
-    ts[i + 1] = ts[i] + ((L.ops[i].M + bm - 1) / bm) * ((L.ops[i].N + bn - 1) / bn);
-  L.d.tile = tile;
-  L.d.splitk = 1;
-  L.grid = std::min(ts[n], 512);
+    L.tile_start[i + 1] =
+        L.tile_start[i] + ((L.ops[i].M + bm - 1) / bm) * ((L.ops[i].N + bn - 1) / bn);
   BHIP(b, hipMemcpyAsync(L.d_ops, L.ops.data(), n * sizeof(GemmOp), hipMemcpyHostToDevice, b->stream));
-  BHIP(b, hipMemcpyAsync(L.d_tiles, ts.data(), (n + 1) * sizeof(int), hipMemcpyHostToDevice, b->stream));
+  BHIP(b, hipMemcpyAsync(L.d_tiles, L.tile_start.data(), (n + 1) * sizeof(int),
+                         hipMemcpyHostToDevice, b->stream));
   BHIP(b, hipMemcpyAsync((void*)L.d_done, L.done.data(), n * sizeof(int*), hipMemcpyHostToDevice,
                          b->stream));
-  BHIP(b, hipStreamSynchronize(b->stream));
   return OMM_OK;
 }
 
 int launch_list(omm_batch* b, OpList& L) {
   if (L.ops.empty()) return OMM_OK;
-  BHIP(b, gemm_grouped_launch(L.d, L.d_ops, L.d_tiles, L.d_done, (int)L.ops.size(), L.grid,
-                              b->stream));
-  return OMM_OK;
-}
-
-// Times the grouped launch with each macro tile once (after a warm-up) and keeps the fastest.
-int tune_list(omm_batch* b, OpList& L) {
-  if (L.ops.empty() || L.tuned) return OMM_OK;
-  hipEvent_t e0, e1;
-  BHIP(b, hipEventCreate(&e0));
-  BHIP(b, hipEventCreate(&e1));
-  float best = 1e30f;
-  int best_t = 0;
-  for (int t = 0; t < gemm_grouped_num_tiles(); ++t) {
-    BTRY(upload_list(b, L, t));
-    BTRY(launch_list(b, L));
-    BHIP(b, hipEventRecord(e0, b->stream));
-    BTRY(launch_list(b, L));
-    BHIP(b, hipEventRecord(e1, b->stream));
-    BHIP(b, hipEventSynchronize(e1));
-    float ms = 0.f;
-    BHIP(b, hipEventElapsedTime(&ms, e0, e1));
-    if (ms < best) {
-      best = ms;
-      best_t = t;
-    }
-  }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  BTRY(upload_list(b, L, best_t));
-  L.tuned = true;
+  BHIP(b, gemm_grouped_launch(L.d, L.d_ops, L.d_tiles, L.d_done, (int)L.ops.size(),
+                              L.tile_start.back(), b->stream));
   return OMM_OK;
 }
 
@@ -317,13 +286,12 @@ int build_lists(omm_batch* b, bool f64) {
   for (OpList* l : L.all()) {
     l->ops.clear();
     l->done.clear();
-    l->tuned = false;
   }
   const int cm = f64 ? CF64 : CF32, tw = f64 ? T_F64 : T_F32;
   L.init1.d = GemmDesc{cm, tw, tw, tw, tw, KC, KC, 0, 1};
   L.init2.d = GemmDesc{cm, tw, tw, T_F64, T_F64, KC, KC, 0, 1};
   for (int p = 0; p < 2; ++p) {
-    L.grad[p].d = GemmDesc{cm, T_F64, tw, tw, tw, KC, RC, 0, 1};
+    L.grad[p].d = GemmDesc{cm, T_F64, tw, tw, tw, RC, RC, 0, 1};  // HW, SW are symmetric
     L.pg[p].d = GemmDesc{cm, tw, tw, tw, tw, KC, KC, 0, 1};
   }
   L.hdsd.d = GemmDesc{cm, tw, tw, tw, tw, KC, KC, 0, 1};
@@ -349,6 +317,8 @@ int build_lists(omm_batch* b, bool f64) {
     L.init1.ops.push_back(gop(Mo, N, N, C, N, S, N, SC, N));
     L.init2.ops.push_back(gop(Mo, M, N, HC, N, C, N, s.HW, M));
     L.init2.ops.push_back(gop(Mo, M, N, SC, N, C, N, s.SW, M));
+    for (size_t k = L.init2.ops.size() - 2; k < L.init2.ops.size(); ++k)
+      L.init2.ops[k].tri = Mo == M;  // symmetric
     for (int k = 0; k < 2; ++k) L.init1.done.push_back(nullptr), L.init2.done.push_back(nullptr);
     for (int p = 0; p < 2; ++p) {
       void* G = p ? G1 : G0;
@@ -371,9 +341,12 @@ int build_lists(omm_batch* b, bool f64) {
     L.proj.ops.push_back(gop(Mo, M, N, D, N, SC, N, s.S1, M));
     L.proj.ops.push_back(gop(Mo, M, N, D, N, HD, N, s.H2, M));
     L.proj.ops.push_back(gop(Mo, M, N, D, N, SD, N, s.S2, M));
+    for (size_t k = L.proj.ops.size() - 2; k < L.proj.ops.size(); ++k)
+      L.proj.ops[k].tri = Mo == M;  // H'', S'' are symmetric
     for (int k = 0; k < 4; ++k) L.proj.done.push_back(dn);
   }
-  for (OpList* l : L.all()) BTRY(upload_list(b, *l, 1));
+  for (OpList* l : L.all()) BTRY(upload_list(b, *l));
+  BHIP(b, hipStreamSynchronize(b->stream));  // the uploads read host vectors
   return OMM_OK;
 }
 
@@ -461,10 +434,8 @@ int run_phase(omm_batch* b, bool f64, double tol, int max_iter) {
   BTRY(build_lists(b, f64));
 
   // initial products and E_0 of every system
-  BTRY(tune_list(b, L.init1));
   BTRY(launch_list(b, L.init1));
   BTRY(fill_pairs(b, d_sys, 0, 0, false));
-  BTRY(tune_list(b, L.init2));
   BTRY(launch_list(b, L.init2));
   BTRY(fill_pairs(b, d_sys, 1, 0, false));
   BHIP(b, group_energy_init(d_sys, n, b->stream));
@@ -472,26 +443,7 @@ int run_phase(omm_batch* b, bool f64, double tol, int max_iter) {
   bool all_done = true;
   for (int i = 0; i < n; ++i) all_done = all_done && b->st_host[i].done != 0;
   if (max_iter > 0 && !all_done) {
-    // first line search eagerly (autotunes each grouped product while every system is live)
-    BTRY(tune_list(b, L.grad[0]));
-    BTRY(tune_list(b, L.pg[0]));
-    L.grad[1].d.tile = L.grad[0].d.tile;
-    L.pg[1].d.tile = L.pg[0].d.tile;
-    BTRY(upload_list(b, L.grad[1], L.grad[0].d.tile));
-    BTRY(upload_list(b, L.pg[1], L.pg[0].d.tile));
-    BTRY(launch_list(b, L.grad[0]));
-    BTRY(fill_pairs(b, d_sys, 2, 0, true));
-    BTRY(launch_list(b, L.pg[0]));
-    BTRY(fill_pairs(b, d_sys, 3, 0, true));
-    BHIP(b, group_direction(d_sys, n, 0, 1, b->stream));
-    BTRY(tune_list(b, L.hdsd));
-    BTRY(launch_list(b, L.hdsd));
-    BTRY(fill_pairs(b, d_sys, 4, 0, true));
-    BTRY(tune_list(b, L.proj));
-    BTRY(launch_list(b, L.proj));
-    BTRY(fill_pairs(b, d_sys, 5, 0, true));
-    BHIP(b, group_line_search(d_sys, n, b->stream));
-    BHIP(b, group_update(d_sys, n, b->stream));
+    BTRY(batch_iteration(b, L, d_sys, 0));
     // line searches 1 and 2 (parities 1, 0) captured once, replayed until all systems stop
     BHIP(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
     int r1 = batch_iteration(b, L, d_sys, 1);

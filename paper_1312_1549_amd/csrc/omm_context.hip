@@ -232,15 +232,10 @@ void free_plane(Plane& p) {
 }
 
 // ---- tile / split-K choice --------------------------------------------------------------------
-// Heuristic: the largest macro tile that still yields >= 1 workgroup per CU, split-K when even
+// BF16 heuristic: the largest macro tile that still yields >= 1 workgroup per CU, split-K when even
 // the 64x64 tiling leaves CUs idle and K is long. The autotuner replaces it per shape.
 void heuristic_tiling(GemmDesc& d, int M, int N, int K) {
   const int cus = 256;
-  if ((d.compute == CF64 || d.compute == CF32) && (long)M * N <= 65536 && K <= 512) {
-    d.tile = 7;  // one wave per 16 x 16 tile, no staging: a few launches' latency, not a K loop's
-    d.splitk = 1;
-    return;
-  }
   const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
   const long t64 = (long)((M + 63) / 64) * ((N + 63) / 64);
   d.tile = t128 >= cus ? 0 : 1;
@@ -330,8 +325,6 @@ int autotune(omm_ctx* c, GemmDesc d, GemmOp* ops, int nops, int K, std::pair<int
     if (!gemm_supported(dt)) continue;
     const int bm = gemm_tile_rows(t, d.compute), bn = gemm_tile_cols(t, d.compute);
     const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-    // the one-wave tile re-reads its operands per 16 x 16 output tile: small products only
-    if (t == 7 && (tiles > 4096 || K > 2048)) continue;
     if (tiles >= 32 || t == 1) cands.push_back({t, 1});
     for (int sk : {2, 4, 8, 16}) {
       dt.splitk = sk;
@@ -378,8 +371,9 @@ int autotune(omm_ctx* c, GemmDesc d, GemmOp* ops, int nops, int K, std::pair<int
   return OMM_OK;
 }
 
-// One GEMM launch with a tuned (or heuristic) tiling. `tunable` is false for in-place updates,
-// which must not be run more than once.
+// One GEMM launch. FP64 / FP32 products take the small tile direct_choose picks from the sizes; BF16
+// ones a tuned (or heuristic) tiling. `tunable` is false for in-place updates, which must not be
+// run more than once.
 // OMM_TILE=<t> pins every GEMM that supports macro tile t to it (no split-K, no autotuning), and
 // with t >= 4 the FP64 / FP32 GEMMs to tile 4: used to compare tile implementations against
 // each other.
@@ -408,6 +402,8 @@ int gemm(omm_ctx* c, GemmDesc d, GemmOp* ops, int nops, const int* done, bool tu
     // their block-sparse form (so that pinned dense and sparse runs sum in the same order)
     d.tile = 4;
     d.splitk = 1;
+  } else if (!is_bf16_mode(d.compute)) {
+    direct_choose(d, ops, nops);
   } else if (tunable && flops >= 2e9 && autotune_enabled()) {
     TuneKey key{{d.compute, d.ta, d.tb, d.tc, d.tx, d.la, d.lb, M, N, K, nops}};
     std::pair<int, int> choice{-1, 1};
@@ -797,6 +793,8 @@ int initial_products(omm_ctx* c, Work<T>& w, int compute, const T* Hs, const T* 
   GemmDesc d2{compute, et, et, T_F64, T_F64, KC, KC, 0, 1};
   GemmOp ops2[2] = {make_op2(Mo, M, N, bf ? pl(c->HC_p) : dn(w.HC, N), Cop, c->HW, M),
                     make_op2(Mo, M, N, bf ? pl(c->SC_p) : dn(w.SC, N), Cop, c->SW, M)};
+  // C Hs C^T and C S C^T are symmetric (square products only: not with paired rows)
+  if (!bf && Mo == M) ops2[0].tri = ops2[1].tri = 1;
   TRY(gemm(c, d2, ops2, 2, nullptr));
   TRY(fill_pairs(c, c->HW, T_F64, M, M, nullptr, false));
   TRY(fill_pairs(c, c->SW, T_F64, M, M, nullptr, false));
@@ -873,8 +871,9 @@ int line_search_iteration(omm_ctx* c, Work<T>& w, int compute, const T* Hs, cons
       TRY(split(c, c->HW, c->HW_p, M, M));
       TRY(split(c, c->SW, c->SW_p, M, M));
     }
-    // BF16x3 reads the transposed planes of SC, HC (k-contiguous); the others read SC, HC by rows
-    GemmDesc d{compute, bf ? T_BF16P : T_F64, ot, tg, et, KC, bf ? KC : RC, 0, 1};
+    // BF16x3 reads the transposed planes of SC, HC (k-contiguous); the others read SC, HC by rows,
+    // and HW, SW (symmetric) by columns, which needs no LDS (omm_gemm_direct.h)
+    GemmDesc d{compute, bf ? T_BF16P : T_F64, ot, tg, et, bf ? KC : RC, bf ? KC : RC, 0, 1};
     GemmOp op = make_op2(Mo, N, M, bf ? pl(c->HW_p) : dn(c->HW, M),
                          bf ? pl(c->SCt_p) : dn(w.SC, N), Gout, N, -4.0, w.HC, N, 8.0);
     const Opnd a2 = bf ? pl(c->SW_p) : dn(c->SW, M), b2 = bf ? pl(c->HCt_p) : dn(w.HC, N);
@@ -1159,6 +1158,7 @@ int resync_fp64(omm_ctx* c) {
                              c->stream));
   GemmOp ops2[2] = {make_op(Mo, M, N, w.HC, N, w.C, N, c->HW, M),
                     make_op(Mo, M, N, w.SC, N, w.C, N, c->SW, M)};
+  if (Mo == M) ops2[0].tri = ops2[1].tri = 1;  // symmetric
   TRY(gemm(c, d, ops2, 2, nullptr));
   TRY(fill_pairs(c, c->HW, T_F64, M, M, nullptr, false));
   TRY(fill_pairs(c, c->SW, T_F64, M, M, nullptr, false));
@@ -1355,22 +1355,26 @@ int c_original(omm_ctx* c, const double** out) {
   return OMM_OK;
 }
 
-// out = scale * C^T X C-style products: rho = 2 C^T (2I - SW) C, EDM = 2 C^T HW C.
-int ct_x_c(omm_ctx* c, const double* Xmm, double diag_for_identity, bool use_identity,
-           double* out) {
+// out = scale C^T Y C + beta Xnn with Y = 2I - SW (rho = 2 C^T (2I - SW) C) or Y = Xmm itself (EDM =
+// 2 C^T HW C): symmetric, so only the upper triangle is computed.
+int ct_x_c(omm_ctx* c, const double* Xmm, bool use_identity, double* out, double scale = 2.0,
+           const double* Xnn = nullptr, double beta = 0.0) {
   const double* Cb = nullptr;
   TRY(c_original(c, &Cb));
   const int M = (int)c->M, N = (int)c->N;
-  double* Y = c->H1;  // M x M scratch
-  if (use_identity) HIPCHK(c, identity_minus(Xmm, Y, M, diag_for_identity, 1.0, c->stream));
-  else HIPCHK(c, copy_f64(Xmm, Y, (int64_t)M * M, c->stream));
+  const double* Y = Xmm;
+  if (use_identity) {
+    HIPCHK(c, identity_minus(Xmm, c->H1, M, 2.0, 1.0, c->stream));
+    Y = c->H1;
+  }
   double* Z = c->w64.HD;  // M x N scratch: Z = Y C
   GemmDesc d{CF64, T_F64, T_F64, T_F64, T_F64, KC, RC, 0, 1};
   GemmOp op = make_op(M, N, M, Y, M, Cb, N, Z, N);
   TRY(gemm(c, d, &op, 1, nullptr));
-  // out = 2 C^T Z : A(m, k) = C[k, m] (RC), B(k, n) = Z[k, n] (RC)
+  // out = scale C^T Z : A(m, k) = C[k, m] (RC), B(k, n) = Z[k, n] (RC)
   GemmDesc d2{CF64, T_F64, T_F64, T_F64, T_F64, RC, RC, 0, 1};
-  GemmOp op2 = make_op(N, N, M, Cb, N, Z, N, out, N, 2.0);
+  GemmOp op2 = make_op(N, N, M, Cb, N, Z, N, out, N, scale, Xnn, N, beta);
+  op2.tri = 1;
   TRY(gemm(c, d2, &op2, 1, nullptr));
   return OMM_OK;
 }
@@ -1690,7 +1694,7 @@ int omm_density_complex(omm_ctx* c, double* rho_re, double* rho_im) {
   TRY(need_minimized(c));
   const int64_t n = c->Nc, n2 = 2 * n;
   TRY(dalloc(c, &c->nn_scratch, (size_t)n2 * n2));
-  TRY(ct_x_c(c, c->SW, 2.0, true, c->nn_scratch));
+  TRY(ct_x_c(c, c->SW, true, c->nn_scratch));
   // rho = rho_hat[:n, :n] + i rho_hat[:n, n:] (the first n rows of the embedded density)
   std::vector<double> top((size_t)n * n2);
   HIPCHK(c, hipMemcpyAsync(top.data(), c->nn_scratch, top.size() * sizeof(double),
@@ -1714,7 +1718,7 @@ int omm_energy(omm_ctx* c, double* E) {
 int omm_density_device(omm_ctx* c, double* d_rho) {
   if (!c || !d_rho) return c ? fail(c, OMM_E_ARG, "null output") : OMM_E_ARG;
   TRY(need_minimized(c));
-  TRY(ct_x_c(c, c->SW, 2.0, true, d_rho));
+  TRY(ct_x_c(c, c->SW, true, d_rho));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return OMM_OK;
 }
@@ -1722,7 +1726,7 @@ int omm_density_device(omm_ctx* c, double* d_rho) {
 int omm_edm_device(omm_ctx* c, double* d_edm) {
   if (!c || !d_edm) return c ? fail(c, OMM_E_ARG, "null output") : OMM_E_ARG;
   TRY(need_minimized(c));
-  TRY(ct_x_c(c, c->HW, 0.0, false, d_edm));
+  TRY(ct_x_c(c, c->HW, false, d_edm));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return OMM_OK;
 }
@@ -1749,11 +1753,9 @@ int omm_backward_device(omm_ctx* c, double gE, double* d_gH, double* d_gS) {
   if (!c || !d_gH || !d_gS) return c ? fail(c, OMM_E_ARG, "null output") : OMM_E_ARG;
   if (d_gH == d_gS) return fail(c, OMM_E_ARG, "d_gH and d_gS must not alias");
   TRY(need_minimized(c));
-  const int64_t nn = c->N * c->N;
-  TRY(ct_x_c(c, c->SW, 2.0, true, d_gH));   // rho
-  TRY(ct_x_c(c, c->HW, 0.0, false, d_gS));  // EDM
-  HIPCHK(c, axpby_f64(d_gS, d_gH, d_gS, -gE, -gE * c->eta_last, nn, c->stream));
-  HIPCHK(c, scale_f64(d_gH, gE, nn, c->stream));
+  // dE/dH = gE rho, dE/dS = -gE EDM - eta dE/dH
+  TRY(ct_x_c(c, c->SW, true, d_gH, 2.0 * gE));
+  TRY(ct_x_c(c, c->HW, false, d_gS, -2.0 * gE, d_gH, -c->eta_last));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return OMM_OK;
 }
@@ -1916,7 +1918,7 @@ extern "C" int omm_backward_device_noalloc(omm_ctx* c, double gE, double* d_gH, 
   double* Z = nullptr;
   TRY(scratch_address(c, &Z));
   const double* C = c->w64.C;
-  // FP64 tile 0 (128 x 128), no split-K: no workspace
+  // no split-K: no workspace
   const GemmDesc dz{CF64, T_F64, T_F64, T_F64, T_F64, KC, RC, 0, 1};   // Z = X[r0:r1] C
   const GemmDesc dc{CF64, T_F64, T_F64, T_F64, T_F64, RC, RC, 0, 1};   // out += C[r0:r1]^T Z
   for (int64_t r0 = 0; r0 < M; r0 += R) {
@@ -1928,12 +1930,16 @@ extern "C" int omm_backward_device_noalloc(omm_ctx* c, double gE, double* d_gH, 
       GemmOp oz = make_op(rows, (int)N, (int)M, X + r0 * M, M, C, N, Z, N,
                           which == 0 ? -1.0 : 1.0, which == 0 ? C + r0 * N : nullptr, N,
                           which == 0 ? 2.0 : 0.0);
-      HIPCHK(c, gemm_launch(dz, &oz, 1, nullptr, nullptr, 0, c->stream));
+      GemmDesc d = dz;
+      direct_choose(d, &oz, 1);
+      HIPCHK(c, gemm_launch(d, &oz, 1, nullptr, nullptr, 0, c->stream));
       // out (+)= (+-2 gE) C[r0:r1]^T Z: A(m, k) = C[r0 + k][m], B(k, n) = Z[k][n]
       const double sc = which == 0 ? 2.0 * gE : -2.0 * gE;
       GemmOp oc = make_op((int)N, (int)N, rows, C + r0 * N, N, Z, N, out, N, sc,
                           r0 > 0 ? out : nullptr, N, r0 > 0 ? 1.0 : 0.0);
-      HIPCHK(c, gemm_launch(dc, &oc, 1, nullptr, nullptr, 0, c->stream));
+      d = dc;
+      direct_choose(d, &oc, 1);
+      HIPCHK(c, gemm_launch(d, &oc, 1, nullptr, nullptr, 0, c->stream));
     }
   }
   // dE/dS = -EDM - eta rho: d_gS = gE (-EDM) - eta (gE rho)

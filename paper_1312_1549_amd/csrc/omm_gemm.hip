@@ -1,6 +1,10 @@
 // GEMM launcher: picks the instantiation for a descriptor, sizes the grid (XCD-remapped tile
 // ids, split-K along y, up to 4 same-shape products along z) and reduces split-K partials in a
 // fixed order.
+#include <math.h>
+
+#include <algorithm>
+
 #include "omm_gemm_impl.h"
 
 namespace omm {
@@ -71,7 +75,41 @@ size_t gemm_ws_bytes(const GemmDesc& d, const GemmOp* ops, int nops) {
 }
 
 int gemm_num_tiles() { return NTILES; }
-int gemm_grouped_num_tiles() { return NTILES_GROUPED; }
+
+// Which small tile an FP64 / FP32 launch takes. A CU works on one tile's MFMAs at a time, so the
+// launch lasts about ceil(tiles / 256) times one tile, at the rate the tile's shape reaches: the
+// shape with the least of that wins (the larger on a tie: fewer operand bytes). Rates relative to
+// the MFMA peak, measured on products that fill the chip evenly (FP64: 384 x 2048 x 2048, 2000 x
+// 13000 x 13000; FP32: 768 x 4096 x 4096 twice in a launch): small tiles ask for more operand bytes
+// per flop, and below three tiles per CU the 32 x 32 one leaves its SIMDs waiting (66 us against 45
+// us with 48 x 48 for the four 384 x 384 x 2048 projections).
+void direct_choose(GemmDesc& d, const GemmOp* ops, int nops) {
+  static const double rate64[NDIRECT] = {0.64, 0.85, 0.93, 0.90, 0.94, 0.97};
+  static const double rate32[NDIRECT] = {0.45, 0.62, 0.75, 0.77, 0.78, 0.85};
+  const double* rate = d.compute == CF64 ? rate64 : rate32;
+  double best = 0.0;
+  for (int i = 0; i < NDIRECT; ++i) {
+    const int bm = DIRECT_BM[i], bn = DIRECT_BN[i];
+    // tiles, weighted by their K relative to the longest one (grouped products differ)
+    double tiles = 0.0;
+    int kmax = 1;
+    for (int o = 0; o < nops; ++o) kmax = std::max(kmax, ops[o].K[0] + (ops[o].nseg > 1 ? ops[o].K[1] : 0));
+    for (int o = 0; o < nops; ++o) {
+      const double tm = (ops[o].M + bm - 1) / bm, tn = (ops[o].N + bn - 1) / bn;
+      const double k = ops[o].K[0] + (ops[o].nseg > 1 ? ops[o].K[1] : 0);
+      // a symmetric product computes the tiles that reach the diagonal
+      tiles += (ops[o].tri ? tm * tn / 2 + std::max(tm, tn) / 2 : tm * tn) * k / kmax;
+    }
+    const double rounds = ceil(tiles / 256.0);
+    const double r = i == 1 && rounds < 3 ? 0.75 * rate[i] : rate[i];
+    const double cost = rounds * bm * bn / r;
+    if (i == 0 || cost <= best) {
+      best = cost;
+      d.tile = DIRECT_TILE0 + i;
+    }
+  }
+  d.splitk = 1;
+}
 
 namespace {
 // Preconditions of the direct-to-LDS tile: 16-byte aligned planes, leading dimensions that are
@@ -107,7 +145,7 @@ sk_fn pick_sk(const GemmDesc& d) {
 bool gemm_supported(const GemmDesc& d) {
   if (d.tile < 0 || d.tile >= NTILES) return false;
   if (d.tile == 6) return d.splitk <= 1 && pick_sk(d) != nullptr;
-  if (d.tile == 7 && d.splitk > 1) return false;
+  if (tile_direct(d.tile) && d.splitk > 1) return false;
   if (d.compute == CF64) return pick_f64(d) != nullptr;
   if (d.compute == CF32) return pick_f32(d) != nullptr;
   if (d.compute == CBF16X3) return pick_bf16x3(d) != nullptr;
@@ -117,13 +155,15 @@ bool gemm_supported(const GemmDesc& d) {
 }
 
 hipError_t gemm_grouped_launch(const GemmDesc& d, const GemmOp* d_ops, const int* d_tile_start,
-                               const int* const* d_done, int nops, int grid, hipStream_t s) {
-  if ((d.compute != CF32 && d.compute != CF64) || nops < 1 || grid < 1)
+                               const int* const* d_done, int nops, int tiles, hipStream_t s) {
+  if ((d.compute != CF32 && d.compute != CF64) || nops < 1 || tiles < 1 || !tile_direct(d.tile))
     return hipErrorInvalidValue;
   grouped_fn fn = d.compute == CF64 ? pick_grouped_f64(d) : pick_grouped_f32(d);
   if (!fn) return hipErrorInvalidValue;
   GroupedArgs g{d_ops, d_tile_start, d_done, nops};
-  hipLaunchKernelGGL(fn, dim3(grid), dim3(tile_threads(d.tile, d.compute)), 0, s, g);
+  // whole rounds of 8 XCDs x 16 tiles
+  hipLaunchKernelGGL(fn, dim3((tiles + 127) / 128 * 128), dim3(tile_threads(d.tile, d.compute)), 0,
+                     s, g);
   return hipGetLastError();
 }
 
@@ -195,6 +235,7 @@ hipError_t launch_products(const GemmDesc& d, const GemmOp* ops, int nops, const
     dd.tile = 4;  // same 256 x 256 tile on the register path, one workgroup per tile
     dd.splitk = 1;
   }
+  if (tile_direct(dd.tile) && dd.splitk > 1) return hipErrorInvalidValue;
   if (dd.tile == 5 && !dma_ok(dd, ops, nops)) dd.tile = 4;  // same 256 x 256 tile, register path
   gemm_fn fn = nullptr;
   if (dd.compute == CF64) fn = pick_f64(dd);
@@ -235,8 +276,8 @@ hipError_t gemm_launch(const GemmDesc& d, const GemmOp* ops, int nops, const int
     tri = true;
   }
   hipError_t e = launch_products(d, ops, nops, done, ws, ws_bytes, s);
-  // the one-wave tile writes both halves of a symmetric result itself
-  if (e != hipSuccess || !tri || ops[0].M <= 0 || d.tile == 7) return e;
+  // the small tiles write both halves of a symmetric result themselves
+  if (e != hipSuccess || !tri || ops[0].M <= 0 || tile_direct(d.tile)) return e;
   GemmBatch b;
   for (int i = 0; i < nops; ++i) b.op[i] = ops[i];
   const int nb = (ops[0].M + 31) / 32;

@@ -1081,99 +1081,14 @@ __global__ __launch_bounds__(WM* WN * 64, MINW) void gemm_kernel(GemmBatch batch
                                                                   ws, blockIdx.z, gridDim.z);
 }
 
-// Tiny products (FP64 and FP32 modes, a few hundred outputs a side, K of a few hundred): one wave
-// per 16 x 16 output tile, operands read from memory straight into MFMA fragments (lane l holds
-// A(i0 + l % 16, k + l / 16) and B(k + l / 16, j0 + l % 16)), the loads of KU 4-deep K steps
-// issued before their MFMAs. A staged macro tile spends such a product waiting on its K loop.
-template <int MODE, typename TA, typename TB, typename TC, typename TX, int LA, int LB>
-__global__ __launch_bounds__(64) void gemm_kernel_tiny(GemmBatch batch, const int* done,
-                                                       int nsplit, double* ws) {
-  static_assert(MODE == CF64 || MODE == CF32, "FP64 / FP32 MFMA fragments");
-  typedef typename AccT<MODE>::type acc_t;
-  typedef typename std::conditional<MODE == CF64, double, float>::type mt;
-  if (done && *done) return;
-  const GemmOp& op = batch.op[blockIdx.z];
-  const int tiles_m = (op.M + 15) / 16, tiles_n = (op.N + 15) / 16;
-  int tm, tn;
-  if (!tile_of(tiles_m, tiles_n, tm, tn)) return;
-  if (op.tri && tm > tn) return;  // written by its mirror tile
-  const int lane = threadIdx.x, li = lane & 15, lk = lane >> 4;
-  const int i = tm * 16 + li, j = tn * 16 + li;
-  acc_t acc[1][1];
-  acc[0][0] = acc_t{0, 0, 0, 0};
-  constexpr int KU = 32;
-  for (int seg = 0; seg < op.nseg; ++seg) {
-    const TA* A = static_cast<const TA*>(op.A[seg]);
-    const TB* B = static_cast<const TB*>(op.B[seg]);
-    const int64_t lda = op.lda[seg], ldb = op.ldb[seg];
-    const int K = op.K[seg];
-    for (int k0 = 0; k0 < K; k0 += 4 * KU) {
-      mt a[KU], b[KU];
-#pragma unroll
-      for (int u = 0; u < KU; ++u) {
-        const int k = k0 + 4 * u + lk;
-        const bool kin = k < K;
-        a[u] = kin && i < op.M
-                   ? (mt)(LA == KC ? A[(int64_t)i * lda + k] : A[(int64_t)k * lda + i])
-                   : (mt)0;
-        b[u] = kin && j < op.N
-                   ? (mt)(LB == KC ? B[(int64_t)j * ldb + k] : B[(int64_t)k * ldb + j])
-                   : (mt)0;
-      }
-#pragma unroll
-      for (int u = 0; u < KU; ++u) acc[0][0] = mfma4(a[u], b[u], acc[0][0]);
-    }
-  }
-  if (op.tri) {
-    // symmetric result: each upper element is also stored to its mirror, in place of the
-    // separate mirror pass of the staged tiles
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int rr = MODE == CF64 ? lk + 4 * r : 4 * lk + r;
-      const int row = tm * 16 + rr, col = tn * 16 + li;
-      if (row < op.M && col < op.N && row <= col) {
-        double v = op.alpha * (double)acc[0][0][r];
-        if (op.X) v += op.beta * (double)ldg<TX>(op.X, (int64_t)row * op.ldx + col);
-        store_out<TC>(op, row, col, v);
-        if (row < col) store_out<TC>(op, col, row, v);
-      }
-    }
-    return;
-  }
-  store_acc<MODE, TC, TX, 1, 1>(op, acc, tm * 16, tn * 16, lane, 0, 1, ws, blockIdx.z,
-                                gridDim.z);
-}
-
-// Grouped products of uneven shapes: a persistent grid walks the concatenated tile list of all
-// ops (tile_start = prefix sums); an op whose `done` flag is set is skipped.
+// Grouped products of uneven shapes: the concatenated tile lists of all ops (tile_start = prefix
+// sums); an op whose `done` flag is set is skipped.
 struct GroupedArgs {
   const GemmOp* ops;
   const int* tile_start;  // nops + 1 entries
   const int* const* done; // per op, nullable entries
   int nops;
 };
-
-template <int MODE, typename TA, typename TB, typename TC, typename TX, int LA, int LB, int WM,
-          int WN, int TM, int TN, int BK, int MINW, bool SWZ = false>
-__global__ __launch_bounds__(WM* WN * 64, MINW) void gemm_grouped_kernel(GroupedArgs g) {
-  constexpr int BM = WM * TM * 16, BN = WN * TN * 16;
-  const int total = g.tile_start[g.nops];
-  for (int t = blockIdx.x; t < total; t += gridDim.x) {
-    int lo = 0, hi = g.nops - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (g.tile_start[mid] <= t) lo = mid; else hi = mid - 1;
-    }
-    const int* dn = g.done[lo];
-    if (dn && *dn) continue;
-    const GemmOp& op = g.ops[lo];  // by reference: a local copy would sit in scratch memory
-    const int tiles_m = (op.M + BM - 1) / BM;
-    const int local = t - g.tile_start[lo];
-    gemm_tile<MODE, TA, TB, TC, TX, LA, LB, WM, WN, TM, TN, BK, SWZ>(
-        op, local % tiles_m, local / tiles_m, 0, 1, nullptr, 0, 1);
-    __syncthreads();  // LDS is reused by the next tile
-  }
-}
 
 typedef void (*grouped_fn)(GroupedArgs);
 typedef void (*sk_fn)(GemmBatch, const int*, SkArgs, float*);
@@ -1191,36 +1106,25 @@ sk_fn pick_sk_kernel() {
 // two-product modes, 2 for BF16x3).
 //    6: tile 5 on a stream-K schedule (persistent, whole-tile rounds, then the remaining tiles
 //       cut evenly across the workgroups).
-//    7: FP64 / FP32 only: 16 x 16, one wave per tile, fragments loaded from memory
-//       (gemm_kernel_tiny), no split-K.
-constexpr int NTILES = 8;
-constexpr int NTILES_GROUPED = 5;
+//    7 .. 12: FP64 / FP32 only: the small tiles of omm_gemm_direct.h, 16x32, 32x32, 48x48, 48x64,
+//       64x64 and 64x96, no split-K.
+constexpr int DIRECT_TILE0 = 7, NDIRECT = 6;
+constexpr int NTILES = DIRECT_TILE0 + NDIRECT;
+constexpr int DIRECT_BM[NDIRECT] = {16, 32, 48, 48, 64, 64};
+constexpr int DIRECT_BN[NDIRECT] = {32, 32, 48, 64, 64, 96};
+inline bool tile_direct(int t) { return t >= DIRECT_TILE0; }
 inline bool tile_big(int t, int mode) { return t >= 4 && is_bf16_mode(mode); }
 inline int tile_bm(int t, int mode) {
-  return t == 7 ? 16 : t == 1 ? 64 : (t == 2 || tile_big(t, mode) ? 256 : 128);
+  if (tile_direct(t)) return DIRECT_BM[t - DIRECT_TILE0];
+  return t == 1 ? 64 : (t == 2 || tile_big(t, mode) ? 256 : 128);
 }
 inline int tile_bn(int t, int mode) {
-  return t == 7 ? 16 : t == 1 ? 64 : (t == 3 || tile_big(t, mode) ? 256 : 128);
+  if (tile_direct(t)) return DIRECT_BN[t - DIRECT_TILE0];
+  return t == 1 ? 64 : (t == 3 || tile_big(t, mode) ? 256 : 128);
 }
 inline int tile_threads(int t, int mode) {
-  return t == 7 ? 64 : (t == 2 || t == 3 || tile_big(t, mode)) ? 512 : 256;
-}
-
-template <int MODE, typename TA, typename TB, typename TC, typename TX, int LA, int LB>
-grouped_fn pick_grouped_tile(int tile) {
-  constexpr int BK = is_bf16_mode(MODE) ? 32 : 16;
-  switch (tile) {
-    case 0: return gemm_grouped_kernel<MODE, TA, TB, TC, TX, LA, LB, 2, 2, 4, 4, BK, 1>;
-    case 1: return gemm_grouped_kernel<MODE, TA, TB, TC, TX, LA, LB, 2, 2, 2, 2, BK, 2>;
-    case 2: return gemm_grouped_kernel<MODE, TA, TB, TC, TX, LA, LB, 4, 2, 4, 4, BK, 1>;
-    case 3: return gemm_grouped_kernel<MODE, TA, TB, TC, TX, LA, LB, 2, 4, 4, 4, BK, 1>;
-    case 4:
-      if constexpr (is_bf16_mode(MODE))
-        return gemm_grouped_kernel<MODE, TA, TB, TC, TX, LA, LB, 2, 4, 8, 4, BK, 1, true>;
-      else
-        return gemm_grouped_kernel<MODE, TA, TB, TC, TX, LA, LB, 2, 2, 4, 4, BK, 2>;
-    default: return nullptr;
-  }
+  if (tile_direct(t)) return 256;
+  return (t == 2 || t == 3 || tile_big(t, mode)) ? 512 : 256;
 }
 
 template <int MODE, typename TA, typename TB, typename TC, typename TX, int LA, int LB>
@@ -1240,11 +1144,6 @@ gemm_fn pick_tile(int tile) {
       if constexpr (is_bf16_mode(MODE) && std::is_same<TA, unsigned short>::value &&
                     std::is_same<TB, unsigned short>::value && LA == KC && LB == KC)
         return gemm_kernel_dma<MODE, TC, TX, dma_stages(MODE)>;
-      else
-        return nullptr;
-    case 7:
-      if constexpr (MODE == CF64 || MODE == CF32)
-        return gemm_kernel_tiny<MODE, TA, TB, TC, TX, LA, LB>;
       else
         return nullptr;
     default: return nullptr;

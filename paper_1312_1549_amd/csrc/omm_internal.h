@@ -76,7 +76,7 @@ struct GemmDesc {
   int compute;         // Compute
   int ta, tb, tc, tx;  // ElemType of A, B, C, X
   int la, lb;          // Layout of A, B
-  int tile;            // macro tile, see gemm_tile_rows / gemm_tile_cols (0..6)
+  int tile;            // macro tile, see gemm_tile_rows / gemm_tile_cols (0..12)
   int splitk;          // >1: K split across workgroups, partials reduced in FP64 (needs ws)
 };
 
@@ -101,15 +101,16 @@ hipError_t block_pattern(const double* B, int64_t n, unsigned char* flags, hipSt
 void embed_operator(const double* re, const double* im, int64_t n, std::vector<double>& out);
 void embed_rows(const double* re, const double* im, int64_t m, int64_t n, std::vector<double>& out);
 int gemm_num_tiles();
-int gemm_grouped_num_tiles();
 bool gemm_supported(const GemmDesc& d);
 int gemm_tile_rows(int tile, int mode);
 int gemm_tile_cols(int tile, int mode);
-// Grouped FP32 or FP64 products of uneven shapes in one persistent launch of `grid` workgroups.
-// All arrays are device memory: nops ops, tile prefix sums (nops + 1, computed with the tile
-// shape of d.tile), per-op done flags (entries nullable). No split-K.
+// The tile of an FP64 / FP32 launch of `nops` products (same or uneven shapes): sets d.tile, d.splitk.
+void direct_choose(GemmDesc& d, const GemmOp* ops, int nops);
+// Grouped FP32 or FP64 products of uneven shapes in one launch of one workgroup per tile. All arrays
+// are device memory: nops ops, tile prefix sums (nops + 1, computed with the tile shape of d.tile,
+// a small tile; `tiles` is the last), per-op done flags (entries nullable). No split-K.
 hipError_t gemm_grouped_launch(const GemmDesc& d, const GemmOp* d_ops, const int* d_tile_start,
-                               const int* const* d_done, int nops, int grid, hipStream_t s);
+                               const int* const* d_done, int nops, int tiles, hipStream_t s);
 
 // ---- elementwise / reduction kernels (omm_kernels.hip) ----
 // Number of per-block partial sums each reduction writes is at most RED_BLOCKS.
@@ -190,7 +191,6 @@ hipError_t identity_minus(const double* SW, double* out, int M, double diag, dou
                           hipStream_t s);
 hipError_t axpby_f64(const double* a, const double* b, double* out, double ca, double cb, int64_t n,
                      hipStream_t s);
-hipError_t scale_f64(double* a, double c, int64_t n, hipStream_t s);
 
 // ---- grouped (batched) stages: one launch over many systems, blockIdx.y = system ----
 struct SysDev {

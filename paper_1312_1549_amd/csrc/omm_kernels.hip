@@ -974,11 +974,6 @@ __global__ void k_axpby(const double* a, const double* b, double* out, double ca
     out[i] = ca * a[i] + cb * b[i];
 }
 
-__global__ void k_scale(double* a, double c, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT)
-    a[i] *= c;
-}
-
 // ---- grouped kernels (blockIdx.y = system) -----------------------------------------------------
 __global__ void g_energy_partials(const SysDev* sys) {
   const SysDev& d = sys[blockIdx.y];
@@ -1363,11 +1358,6 @@ hipError_t identity_minus(const double* SW, double* out, int M, double diag, dou
 hipError_t axpby_f64(const double* a, const double* b, double* out, double ca, double cb, int64_t n,
                      hipStream_t s) {
   hipLaunchKernelGGL(k_axpby, dim3(ew_blocks(n)), dim3(NT), 0, s, a, b, out, ca, cb, n);
-  return hipGetLastError();
-}
-
-hipError_t scale_f64(double* a, double c, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale, dim3(ew_blocks(n)), dim3(NT), 0, s, a, c, n);
   return hipGetLastError();
 }
 
