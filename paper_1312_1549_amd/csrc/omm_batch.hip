@@ -205,13 +205,12 @@ int setup_sys(omm_batch* b, BSys& s, double eta, double tau, bool need32) {
         b->inv_cap = need;
       }
       int bad = 0;
-      BHIP(b, invert_in_place(s.P64, s.N, b->inv_work, b->stream, &bad));
+      BHIP(b, invert_symmetric(s.P64, s.N, b->inv_work, b->stream, &bad));
       if (bad) {
         s.p_kind = -1;
         return bfail(b, OMM_E_PRECON, "preconditioner inversion hit a singular pivot block or a "
                                       "non-finite value");
       }
-      BHIP(b, symmetrize(s.P64, s.N, b->stream));
       double res = 0.0;
       BHIP(b, inverse_residual(s.P64, s.S, kind == 2 ? s.T : nullptr, 1.0 / tau, s.N, b->inv_work,
                                b->stream, &res));

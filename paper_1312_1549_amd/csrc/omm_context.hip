@@ -536,20 +536,25 @@ bool sparse_products(const omm_ctx* c) {
   return c->sparse && c->mode == OMM_BF16X3 && !reduced(c);
 }
 
+// Scratch of the factorizations (one size for all of them: the buffer is allocated once).
+int ensure_inv_work(omm_ctx* c) {
+  return dalloc(c, &c->inv_work, std::max({invert_work_doubles(c->N), inverse_residual_work_doubles(c->N),
+                                          cholesky_work_doubles(c->N)}));
+}
+
 // S = L L^T and L^-1 for the Cholesky-reduced flavour (Sec. 2.4), once per S.
 int prepare_cholesky(omm_ctx* c) {
   if (c->l_valid) return OMM_OK;
   const size_t nn = (size_t)c->N * c->N;
   TRY(dalloc(c, &c->L, nn));
   TRY(dalloc(c, &c->Linv, nn));
-  TRY(dalloc(c, &c->inv_work, std::max(invert_work_doubles(c->N), cholesky_work_doubles())));
-  HIPCHK(c, copy_f64(c->S, c->L, (int64_t)nn, c->stream));
+  TRY(dalloc(c, &c->nn_scratch, nn));
+  TRY(ensure_inv_work(c));
+  HIPCHK(c, copy_f64(c->S, c->nn_scratch, (int64_t)nn, c->stream));
   int bad = 0;
-  HIPCHK(c, cholesky_in_place(c->L, c->N, c->inv_work, c->stream, &bad));
-  if (bad) return fail(c, OMM_E_PRECON, "Cholesky factorization of S failed: S is not positive definite");
-  HIPCHK(c, copy_f64(c->L, c->Linv, (int64_t)nn, c->stream));
-  HIPCHK(c, invert_in_place(c->Linv, c->N, c->inv_work, c->stream, &bad));
-  if (bad) return fail(c, OMM_E_PRECON, "inverting the Cholesky factor hit a zero or non-finite pivot");
+  HIPCHK(c, cholesky_and_inverse(c->nn_scratch, c->L, c->Linv, c->N, c->inv_work, c->stream, &bad));
+  if (bad)
+    return fail(c, OMM_E_PRECON, "Cholesky factorization of S failed: S is not positive definite");
   c->l_valid = true;
   return OMM_OK;
 }
@@ -569,10 +574,12 @@ int prepare_shift(omm_ctx* c, double eta) {
       // X = L^-1 Hs (B(n, k) = Hs[k][n] = Hs[n][k]), then H~ = X L^-T (B(n, k) = L^-1[n][k])
       GemmDesc d{CF64, T_F64, T_F64, T_F64, T_F64, KC, KC, 0, 1};
       GemmOp op = make_op(N, N, N, c->Linv, N, c->Hs, N, c->nn_scratch, N);
+      op.kcut = KCUT_A_TO_M;
       TRY(gemm(c, d, &op, 1, nullptr, true));
       GemmOp op2 = make_op(N, N, N, c->nn_scratch, N, c->Linv, N, c->Hs, N);
+      op2.kcut = KCUT_B_TO_N;
+      op2.tri = 1;
       TRY(gemm(c, d, &op2, 1, nullptr, true));
-      HIPCHK(c, symmetrize(c->Hs, N, c->stream));
     }
     c->hs_valid = true;
     c->hs_eta = eta;
@@ -625,16 +632,14 @@ int prepare_precon(omm_ctx* c, double tau) {
       TRY(dalloc(c, &c->P, nn));
       if (kind == 1) HIPCHK(c, copy_f64(c->S, c->P, (int64_t)nn, c->stream));
       else HIPCHK(c, axpby_f64(c->S, c->T, c->P, 1.0, 1.0 / tau, (int64_t)nn, c->stream));
-      TRY(dalloc(c, &c->inv_work, std::max(invert_work_doubles(c->N),
-                                            inverse_residual_work_doubles(c->N))));
+      TRY(ensure_inv_work(c));
       int bad = 0;
-      HIPCHK(c, invert_in_place(c->P, c->N, c->inv_work, c->stream, &bad));
+      HIPCHK(c, invert_symmetric(c->P, c->N, c->inv_work, c->stream, &bad));
       if (bad) {
         c->p_kind = -1;
         return fail(c, OMM_E_PRECON, "preconditioner inversion hit a singular pivot block or a "
                                      "non-finite value");
       }
-      HIPCHK(c, symmetrize(c->P, c->N, c->stream));
       // the inverse is used only if it inverts: max |X P (S + T/tau) - X| on +-1 probe rows
       double res = 0.0;
       HIPCHK(c, inverse_residual(c->P, c->S, kind == 2 ? c->T : nullptr, 1.0 / tau, c->N,
@@ -1255,6 +1260,7 @@ int minimize_impl(omm_ctx* c, const double* C0, bool C0_device, double eta, doub
       const int M = (int)c->M, N = (int)c->N;
       GemmDesc d{CF64, T_F64, T_F64, T_F64, T_F64, KC, RC, 0, 1};
       GemmOp op = make_op(M, N, N, c->w64.C, N, c->L, N, c->w64.HD, N);
+      op.kcut = KCUT_B_FROM_N;
       TRY(gemm(c, d, &op, 1, nullptr));
       HIPCHK(c, hipMemcpyAsync(c->w64.C, c->w64.HD, mn * sizeof(double), hipMemcpyDeviceToDevice,
                                c->stream));
@@ -1350,6 +1356,7 @@ int c_original(omm_ctx* c, const double** out) {
   TRY(dalloc(c, &c->Corig, (size_t)M * N));
   GemmDesc d{CF64, T_F64, T_F64, T_F64, T_F64, KC, RC, 0, 1};  // B(n, k) = L^-1[k][n]
   GemmOp op = make_op(M, N, N, c->w64.C, N, c->Linv, N, c->Corig, N);
+  op.kcut = KCUT_B_FROM_N;
   TRY(gemm(c, d, &op, 1, nullptr));
   *out = c->Corig;
   return OMM_OK;

@@ -215,7 +215,13 @@ __device__ __forceinline__ void direct_tile(const GemmOp& op, int tm, int tn) {
     // A pair load in the last row of an odd-sized r-contiguous operand reads one element past it:
     // into the next k row, which the last k row does not have, so that row goes to the tail.
     const bool odd = (OA::PAIR && op.M % 2 != 0) || (OB::PAIR && op.N % 2 != 0);
-    const int nfull = (odd ? K - 1 : K) / KS;
+    // the K range of the tile, without the known zeros of a triangular operand (tile origins are
+    // multiples of KS, so the range starts on a whole step)
+    const int kb = op.kcut & KCUT_B_FROM_N ? n0 : 0;
+    int ke = K;
+    if (op.kcut & KCUT_A_TO_M) ke = min(ke, m0 + TM * 16);
+    if (op.kcut & KCUT_B_TO_N) ke = min(ke, n0 + TN * 16);
+    const int nfull = ((odd && ke == K ? K - 1 : ke) - kb) / KS;
     OA oa;
     OB ob;
     oa.init(op.A[seg], op.lda[seg], m0, op.M, lane, smem + w * (OA::RING + OB::RING));
@@ -236,7 +242,7 @@ __device__ __forceinline__ void direct_tile(const GemmOp& op, int tm, int tn) {
     const int cnt = first < nfull ? (nfull - first + WK - 1) / WK : 0;
     if (cnt > 0) {
       // k of this wave's step i (past the end: the last one again, unused)
-      auto kof = [&](int i) { return (first + min(i, cnt - 1) * WK) * KS; };
+      auto kof = [&](int i) { return kb + (first + min(i, cnt - 1) * WK) * KS; };
       // Ring step p holds step i with i % NB == p. Loads into the ring run NB steps ahead of the
       // MFMAs and their fragments are read one step ahead; register loads run NB - 1 ahead.
       auto issue = [&](int q, int i) {  // q = i % NB, known at compile time
@@ -301,9 +307,10 @@ __device__ __forceinline__ void direct_tile(const GemmOp& op, int tm, int tn) {
       });
       if constexpr (LDS) wait_vm<0>();  // nothing lands in the ring after this
     }
-    if (K > nfull * KS && (nfull % WK) == first) {
-      oa.load_tail(nfull * KS, K, m0, op.M, lane);
-      ob.load_tail(nfull * KS, K, n0, op.N, lane);
+    const int kt = kb + nfull * KS;
+    if (ke > kt && (nfull % WK) == first) {
+      oa.load_tail(kt, ke, m0, op.M, lane);
+      ob.load_tail(kt, ke, n0, op.N, lane);
       compute(0, 0, e0, e1);
     }
     first = (first + 1) % WK;

@@ -70,7 +70,12 @@ struct GemmOp {
   // Symmetric result (M == N, no planes): only the tiles on and above the diagonal are computed
   // and the launcher then copies C[j][i] into C[i][j] for every i > j.
   int tri;
+  // KCUT_* bits: known zeros of a triangular operand, skipped by the small tiles (one segment; the
+  // others multiply them).
+  int kcut;
 };
+// A(m, k) = 0 for k > m; B(n, k) = 0 for k > n; B(n, k) = 0 for k < n.
+enum KCut : int { KCUT_A_TO_M = 1, KCUT_B_TO_N = 2, KCUT_B_FROM_N = 4 };
 
 struct GemmDesc {
   int compute;         // Compute
@@ -218,9 +223,10 @@ hipError_t group_pair_rows(const SysDev* d_sys, int nsys, int which, int parity,
                            int max_m, int max_n, hipStream_t s);
 
 // ---- preconditioner (omm_precon.hip) ----
-// In-place inverse of an n x n matrix by a blocked Gauss-Jordan sweep. Returns hipSuccess and
-// sets *bad (host) to 1 if a pivot block was singular or a non-finite value appeared.
-hipError_t invert_in_place(double* A, int64_t n, double* work, hipStream_t s, int* bad);
+// In-place inverse of a symmetric n x n matrix by a blocked sweep; the result is exactly symmetric.
+// Returns hipSuccess and sets *bad (host) to 1 if a pivot block was singular or a non-finite value
+// appeared.
+hipError_t invert_symmetric(double* A, int64_t n, double* work, hipStream_t s, int* bad);
 size_t invert_work_doubles(int64_t n);
 // max_ij |(X P A - X)_ij| over 16 probe rows X of +-1 entries, A = S + inv_tau T (T nullable:
 // A = S), written to *res (host) after a stream synchronization. P, S, T symmetric, n x n.
@@ -229,9 +235,10 @@ hipError_t inverse_residual(const double* P, const double* S, const double* T, d
 size_t inverse_residual_work_doubles(int64_t n);
 // An inverse whose probe residual exceeds this is rejected (OMM_E_PRECON).
 constexpr double INVERSE_RESIDUAL_LIMIT = 1e-8;
-// Cholesky factorization S = L L^T in place (L lower, strict upper set to zero); *bad != 0 when
-// a pivot is not positive (S not positive definite) or the result is not finite.
-hipError_t cholesky_in_place(double* A, int64_t n, double* work, hipStream_t s, int* bad);
-size_t cholesky_work_doubles();
+// Cholesky factorization A = L L^T and the inverse of L (both lower, zeros above); A is overwritten.
+// *bad != 0 when a pivot is not positive (A not positive definite) or a result is not finite.
+hipError_t cholesky_and_inverse(double* A, double* L, double* Linv, int64_t n, double* work, hipStream_t s,
+                                int* bad);
+size_t cholesky_work_doubles(int64_t n);
 
 }  // namespace omm

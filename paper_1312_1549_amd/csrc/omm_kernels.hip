@@ -1164,7 +1164,10 @@ __global__ void k_copy_compare(const double* src, double* dst, int64_t n, int* d
     changed |= __double_as_longlong(v) != __double_as_longlong(dst[i]);
     dst[i] = v;
   }
-  if (__any(changed) && (threadIdx.x & 63) == 0) atomicOr(diff, 1);
+  // one store a wave, and none once another wave's is seen: atomics on one address from every wave
+  // took 66 us at 717 orbitals, 260 us at 2301
+  if (__any(changed) && (threadIdx.x & 63) == 0 && __hip_atomic_load(diff, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+    __hip_atomic_store(diff, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 hipError_t copy_compare_f64(const double* src, double* dst, int64_t n, int* diff, hipStream_t s) {

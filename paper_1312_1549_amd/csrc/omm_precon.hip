@@ -1,22 +1,25 @@
-// One-time FP64 inversion for the preconditioner P = (S + T/tau)^-1 (Sec. 2.4, Eq. 17): an
-// in-place blocked Gauss-Jordan sweep. The paper inverts once per MD step with a library
-// LU, since P need not be positive definite (Sec. 3.1); here each block column costs one
-// pivot-block inversion plus two MFMA GEMMs, so the 2 n^3 flops run on matrix cores.
+// One-time FP64 factorizations.
 //
-// Step for pivot block K (width b), with A the current matrix:
-//   U  = A[:, K] with its diagonal block replaced by A_KK - I      (column panel copy)
-//   W  = A_KK^-1                                                    (one workgroup, in LDS)
-//   A[:, K] = e_K  (zero column panel, identity diagonal block)
-//   R  = W A[K, :]                                                  (b x n GEMM)
-//   A -= U R                                                        (rank-b GEMM update)
-// which leaves A[K,K] = W, A[K,J] = W A_KJ, A[I,K] = -A_IK W and the Schur update elsewhere;
-// after the last block A holds the inverse. The pivot block is inverted by Gauss-Jordan with
+// Preconditioner P = (S + T/tau)^-1 (Sec. 2.4, Eq. 17): a blocked symmetric sweep. The paper inverts
+// once per MD step with a library LU, since P need not be positive definite (Sec. 3.1); here each
+// block column costs one pivot-block inversion plus two MFMA GEMMs. Step for pivot block K (width
+// b), with A the current matrix (symmetric throughout):
+//   U = A[:, K] with its rows of K zero                             (column panel copy)
+//   W = A_KK^-1                                                     (one workgroup, in registers)
+//   V = U W                                                         (n x b GEMM)
+//   A -= V U^T                                                      (rank-b update, upper half)
+//   A[:, K] = V, A[K, :] = V^T, A_KK = -W
+// After the last block A holds minus the inverse. The pivot block is inverted by Gauss-Jordan with
 // partial (row) pivoting inside the block, so an indefinite S + T/tau whose diagonal entries
 // vanish or change sign along the sweep is handled as long as each pivot block is
 // nonsingular; the blocks themselves are not exchanged. A singular pivot block or a non-finite
 // value is reported, and inverse_residual() measures ||A P X - X|| on probe vectors so that a
 // caller can reject an inaccurate inverse instead of using it.
+//
+// Cholesky flavour: S = L L^T and L^-1, block column by block column.
 #include <math.h>
+
+#include <type_traits>
 
 #include "omm_internal.h"
 
@@ -26,9 +29,8 @@ namespace {
 constexpr int NB = 128;
 constexpr int PROBES = 16;  // probe rows of inverse_residual
 
-// U = A[:, k0:k0+b] (ld b) with U[k0+i][i] -= 1; W = A[k0:k0+b, k0:k0+b]; then
-// A[:, k0:k0+b] = e_K.
-__global__ void k_panel(double* A, int64_t n, int64_t k0, int b, double* U, double* W) {
+// U = A[:, k0:k0+b] (ld b) with zeros in the rows of the block, W = A[k0:k0+b, k0:k0+b].
+__global__ void k_panel(const double* A, int64_t n, int64_t k0, int b, double* U, double* W) {
   const int64_t total = n * b;
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * 256) {
@@ -36,131 +38,158 @@ __global__ void k_panel(double* A, int64_t n, int64_t k0, int b, double* U, doub
     const int j = (int)(e % b);
     const double v = A[i * n + k0 + j];
     const bool diag_blk = i >= k0 && i < k0 + b;
-    U[e] = (diag_blk && i - k0 == j) ? v - 1.0 : v;
+    U[e] = diag_blk ? 0.0 : v;
     if (diag_blk) W[(i - k0) * b + j] = v;
-    A[i * n + k0 + j] = (diag_blk && i - k0 == j) ? 1.0 : 0.0;
   }
 }
 
-// In-place inverse of the b x b block W (b <= NB = 128) by Gauss-Jordan with partial row
-// pivoting, one workgroup of 1024 threads. Thread t holds column j = t % 128 of rows
-// g + 8 k (g = t / 128, k = 0..15) in registers; LDS carries only what a step shares: the
-// pivot candidates, the pivot row and the pivot column. Step p: the row r >= p of largest
-// |W[r][p]| is exchanged with row p (perm[p] = r), then the usual in-place elimination with that
-// pivot. Pivoting the rows yields (P W)^-1 = W^-1 P^T, so the column exchanges are undone in
-// reverse order: column c of the result is the eliminated column src[c]. A zero or non-finite
-// pivot sets *bad.
-constexpr int GJ_RPT = NB / 8;  // rows per thread
-
-// w[k] for a k known only at run time, selected without indexing the register array
-__device__ __forceinline__ double gj_get(const double (&w)[GJ_RPT], int k) {
-  double v = 0.0;
-#pragma unroll
-  for (int q = 0; q < GJ_RPT; ++q) v = q == k ? w[q] : v;
-  return v;
-}
-__device__ __forceinline__ void gj_set(double (&w)[GJ_RPT], int k, double v) {
-#pragma unroll
-  for (int q = 0; q < GJ_RPT; ++q) w[q] = q == k ? v : w[q];
-}
-
-__global__ __launch_bounds__(1024) void k_small_gj(double* W, int b, int* bad) {
-  __shared__ double rowp[NB], colp[NB], rowr[NB];
-  __shared__ double cv[8];
-  __shared__ int ci[8];
-  __shared__ int perm[NB], src[NB];
-  __shared__ int piv_row;
-  const int tid = threadIdx.x, j = tid & (NB - 1), g = tid >> 7;
-  double w[GJ_RPT];
-#pragma unroll
-  for (int k = 0; k < GJ_RPT; ++k) {
-    const int i = g + 8 * k;
-    w[k] = (i < b && j < b) ? W[i * b + j] : 0.0;
-  }
-  for (int p = 0; p < b; ++p) {
-    // pivot search in column p: the eight threads holding it reduce their rows >= p
-    if (j == p) {
-      double best = -1.0;
-      int br = p;
-#pragma unroll
-      for (int k = 0; k < GJ_RPT; ++k) {
-        const int i = g + 8 * k;
-        const double v = fabs(w[k]);
-        if (i >= p && i < b && v > best) {
-          best = v;
-          br = i;
-        }
-      }
-      cv[g] = best;
-      ci[g] = br;
+// A[:, k0:k0+b] = V and A[k0:k0+b, :] = V^T outside the block, A_KK = -(W + W^T) / 2; 32 x 32 tiles
+// of V (rows blockIdx.x, columns blockIdx.y), transposed through LDS.
+__global__ __launch_bounds__(256) void k_sweep_write(double* A, int64_t n, int64_t k0, int b,
+                                                     const double* V, const double* W) {
+  __shared__ double t[32][33];
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int64_t i0 = (int64_t)blockIdx.x * 32;
+  const int j0 = blockIdx.y * 32;
+  for (int r = ty; r < 32; r += 8) {
+    const int64_t i = i0 + r;
+    const int j = j0 + tx;
+    if (i < n && j < b) {
+      const bool diag_blk = i >= k0 && i < k0 + b;
+      const int64_t p = i - k0;
+      const double v = diag_blk ? -0.5 * (W[p * b + j] + W[j * b + p]) : V[i * b + j];
+      t[r][tx] = v;
+      A[i * n + k0 + j] = v;
     }
-    __syncthreads();
-    if (tid == 0) {
-      double best = cv[0];
-      int br = ci[0];
-      for (int q = 1; q < 8; ++q)
-        if (cv[q] > best || (cv[q] == best && ci[q] < br)) {
-          best = cv[q];
-          br = ci[q];
-        }
-      piv_row = br;
-      perm[p] = br;
-    }
-    __syncthreads();
-    const int r = piv_row;
-    const int gp = p & 7, kp = p >> 3, gr = r & 7, kr = r >> 3;
-    // rows p and r through LDS: row p's old values to rowp, row r's to rowr
-    if (g == gp) rowp[j] = gj_get(w, kp);
-    if (g == gr) rowr[j] = gj_get(w, kr);
-    __syncthreads();
-    if (r != p) {
-      if (g == gp) gj_set(w, kp, rowr[j]);
-      if (g == gr) gj_set(w, kr, rowp[j]);
-    }
-    __syncthreads();
-    // the pivot row (after the exchange) and the pivot column
-    if (g == gp) rowp[j] = gj_get(w, kp);
-    if (j == p)
-#pragma unroll
-      for (int k = 0; k < GJ_RPT; ++k) colp[g + 8 * k] = w[k];
-    __syncthreads();
-    const double d = rowp[p];
-    if (tid == 0 && (!(fabs(d) > 0.0) || !isfinite(d))) atomicOr(bad, 1);
-    const double ip = 1.0 / d;
-    const double rj = rowp[j];
-#pragma unroll
-    for (int k = 0; k < GJ_RPT; ++k) {
-      const int i = g + 8 * k;
-      const double ci_ = colp[i];
-      double v;
-      if (i == p && j == p) v = ip;
-      else if (i == p) v = rj * ip;
-      else if (j == p) v = -ci_ * ip;
-      else v = w[k] - ci_ * rj * ip;
-      w[k] = v;
-    }
-    __syncthreads();  // rowp, colp and the candidates are rewritten by the next step
-  }
-  // undo the row exchanges as column exchanges, last first: output column c = column src[c]
-  if (tid == 0) {
-    for (int c = 0; c < b; ++c) src[c] = c;
-    for (int p = b - 1; p >= 0; --p) {
-      const int r = perm[p];
-      const int t = src[p];
-      src[p] = src[r];
-      src[r] = t;
-    }
-    for (int c = 0; c < b; ++c) perm[src[c]] = c;  // perm now maps a source column to its output
   }
   __syncthreads();
-  if (j < b) {
-    const int c = perm[j];
+  for (int r = ty; r < 32; r += 8) {
+    const int64_t i = i0 + tx;
+    const int j = j0 + r;
+    if (i < n && j < b && !(i >= k0 && i < k0 + b)) A[(k0 + j) * n + i] = t[tx][r];
+  }
+}
+
+// The b x b blocks (b <= NB = 128) below are worked by 256 threads in registers: thread (ti, tj) holds
+// the 8 x 8 elements of rows ti + 16 a and columns tj + 16 c. The elimination is a chain of b
+// dependent steps, so what counts is the latency of one: LDS carries a step's pivot column and row
+// (BLK_LD doubles per ti or tj: 16-byte aligned, on different banks), and the loop over c is
+// unrolled, so that every register index is known.
+constexpr int BLK_LD = 10;
+
+__device__ __forceinline__ void blk_read(double (&v)[8], const double* src) {
 #pragma unroll
-    for (int k = 0; k < GJ_RPT; ++k) {
-      const int i = g + 8 * k;
-      if (i < b) W[i * b + c] = w[k];
+  for (int k = 0; k < 8; k += 2) {
+    const double2 q = *reinterpret_cast<const double2*>(src + k);
+    v[k] = q.x;
+    v[k + 1] = q.y;
+  }
+}
+
+// Largest value over the 16 lanes of a DPP row, in every lane of it.
+__device__ __forceinline__ unsigned row16_max(unsigned v) {
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, false));  // row_ror:8
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xf, 0xf, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xf, 0xf, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xf, 0xf, false));
+  return v;
+}
+
+// In-place inverse of W by Gauss-Jordan with partial row pivoting. Step p eliminates column p with
+// the row r of largest |W[r][p]| (to 13 bits of the mantissa) among the rows not used yet; no row
+// is moved: row r of the eliminated matrix is row p of the inverse, and its column q is column
+// r_q. Two barriers a step: the pivot column, in which every wave finds the pivot for itself (its
+// 16 row groups hold all rows), and the pivot row. A zero or non-finite pivot sets *bad.
+// 188 us for a 128 x 128 block (five barriers a step and exchanged rows took 560 us).
+__global__ __launch_bounds__(256) void k_small_gj(double* W, int b, int* bad) {
+  __shared__ __attribute__((aligned(16))) double colp[16 * BLK_LD], rowp[16 * BLK_LD];
+  __shared__ int row_of[NB], step_of[NB];  // pivot row of a step, step of a row
+  const int tid = threadIdx.x, ti = tid & 15, tj = tid >> 4;
+  double w[8][8];
+  unsigned used = 0;  // bit a: row ti + 16 a is not a candidate
+#pragma unroll
+  for (int a = 0; a < 8; ++a) {
+    if (ti + 16 * a >= b) used |= 1u << a;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int i = ti + 16 * a, j = tj + 16 * c;
+      w[a][c] = i < b && j < b ? W[i * b + j] : 0.0;
     }
   }
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    for (int s = 0; s < 16; ++s) {
+      const int p = 16 * c + s;
+      if (p >= b) break;
+      if (tj == s)
+#pragma unroll
+        for (int a = 0; a < 8; ++a) colp[ti * BLK_LD + a] = w[a][c];
+      __syncthreads();
+      double ca[8];
+      blk_read(ca, colp + ti * BLK_LD);
+      unsigned key = 0;
+#pragma unroll
+      for (int a = 0; a < 8; ++a) {
+        const unsigned hi = (unsigned)__double2hiint(ca[a]) & 0x7fffff80u;
+        const unsigned k = (used >> a & 1) ? 0u : (0x80000000u | hi | (unsigned)(127 - (ti + 16 * a)));
+        key = max(key, k);
+      }
+      key = (unsigned)__builtin_amdgcn_readfirstlane((int)row16_max(key));
+      const int r = 127 - (int)(key & 127u), tr = r & 15;
+      const double d = colp[tr * BLK_LD + (r >> 4)];
+      // the pivot row goes out and its elements become 0 - (-1) (row / d)
+      auto publish = [&](auto ac) {
+        constexpr int A = decltype(ac)::value;
+        if (ti == tr) {
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            rowp[tj * BLK_LD + k] = w[A][k];
+            w[A][k] = 0.0;
+          }
+          ca[A] = -1.0;
+          used |= 1u << A;
+        }
+      };
+      switch (r >> 4) {
+        case 0: publish(std::integral_constant<int, 0>{}); break;
+        case 1: publish(std::integral_constant<int, 1>{}); break;
+        case 2: publish(std::integral_constant<int, 2>{}); break;
+        case 3: publish(std::integral_constant<int, 3>{}); break;
+        case 4: publish(std::integral_constant<int, 4>{}); break;
+        case 5: publish(std::integral_constant<int, 5>{}); break;
+        case 6: publish(std::integral_constant<int, 6>{}); break;
+        default: publish(std::integral_constant<int, 7>{}); break;
+      }
+      const double ip = 1.0 / d;
+      if (tid == 0) {
+        row_of[p] = r;
+        step_of[r] = p;
+        if (!(fabs(d) > 0.0) || !isfinite(d)) atomicOr(bad, 1);
+      }
+      __syncthreads();
+      double rr[8];
+      blk_read(rr, rowp + tj * BLK_LD);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) rr[k] *= ip;
+      if (tj == s) {  // the pivot column: 0 - c_i / d
+        rr[c] = ip;
+#pragma unroll
+        for (int a = 0; a < 8; ++a) w[a][c] = 0.0;
+      }
+#pragma unroll
+      for (int a = 0; a < 8; ++a)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w[a][k] = fma(-ca[a], rr[k], w[a][k]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < 8; ++a)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int i = ti + 16 * a, j = tj + 16 * c;
+      if (i < b && j < b) W[step_of[i] * b + row_of[j]] = w[a][c];
+    }
 }
 
 // Probe vectors for inverse_residual: X[r][i] = +-1 from an integer hash of (r, i).
@@ -190,62 +219,86 @@ __global__ __launch_bounds__(1024) void k_maxabs(const double* Z, int64_t total,
   if (threadIdx.x == 0) *out = (isfinite(m[0]) ? m[0] : INFINITY);
 }
 
-// Cholesky factorization of the b x b diagonal block at (k0, k0) of A in LDS (lower, right
-// looking); writes L_KK back (zero above the diagonal) and its inverse W = L_KK^-1 (b x b, lower).
-// A pivot that is not positive and finite sets *bad (the block is then garbage, never used).
-__global__ __launch_bounds__(1024) void k_chol_block(double* A, int64_t n, int64_t k0, int b,
-                                                    double* W, int* bad) {
-  __shared__ double a[NB * NB];
-  for (int e = threadIdx.x; e < b * b; e += blockDim.x) a[e] = A[(k0 + e / b) * n + k0 + e % b];
-  __syncthreads();
-  for (int j = 0; j < b; ++j) {
-    if (threadIdx.x == 0) {
-      double d = a[j * b + j];
+// Cholesky factorization of the b x b diagonal block at (k0, k0) of A: writes L_KK to the same place
+// of L (zero above the diagonal) and its inverse to Linv and to W (b x b, lower). Right looking, with the
+// elimination of the unit matrix alongside (row j of x becomes row j of the inverse in step j); one
+// barrier a step, the published column and row being double-buffered. Entries of a column above
+// its diagonal are published as zeros, so finished rows and columns take no updates. A pivot that is
+// not positive and finite sets *bad (the block is then garbage, never used).
+// 128 x 128: 92 us (the factorization in LDS and a forward substitution through memory took 1104).
+__global__ __launch_bounds__(256) void k_chol_block(const double* A, double* L, double* Linv, int64_t n,
+                                                    int64_t k0, int b, double* W, int* bad) {
+  __shared__ __attribute__((aligned(16))) double colp[2][16 * BLK_LD], rowx[2][16 * BLK_LD];
+  const int tid = threadIdx.x, ti = tid & 15, tj = tid >> 4;
+  double l[8][8], x[8][8];
+#pragma unroll
+  for (int a = 0; a < 8; ++a)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int i = ti + 16 * a, j = tj + 16 * c;
+      l[a][c] = i < b && j < b ? A[(k0 + i) * n + k0 + j] : 0.0;
+      x[a][c] = i == j ? 1.0 : 0.0;
+    }
+#pragma unroll
+  for (int o = 0; o < 8; ++o) {
+    for (int s = 0; s < 16; ++s) {
+      const int j = 16 * o + s, buf = s & 1;
+      if (j >= b) break;
+      if (tj == s)
+#pragma unroll
+        for (int a = 0; a < 8; ++a) colp[buf][ti * BLK_LD + a] = ti + 16 * a >= j ? l[a][o] : 0.0;
+      if (ti == s)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          rowx[buf][tj * BLK_LD + c] = x[o][c];
+          x[o][c] = 0.0;
+        }
+      __syncthreads();
+      double ca[8], cb[8], xr[8];
+      blk_read(ca, colp[buf] + ti * BLK_LD);
+      blk_read(cb, colp[buf] + tj * BLK_LD);
+      blk_read(xr, rowx[buf] + tj * BLK_LD);
+      double d = colp[buf][s * BLK_LD + o];
       if (!(d > 0.0) || !isfinite(d)) {
-        atomicOr(bad, 1);
+        if (tid == 0) atomicOr(bad, 1);
         d = 1.0;
       }
-      a[j * b + j] = sqrt(d);
-    }
-    __syncthreads();
-    const double p = a[j * b + j];
-    for (int i = j + 1 + threadIdx.x; i < b; i += blockDim.x) a[i * b + j] /= p;
-    __syncthreads();
-    const int m = b - j - 1;
-    for (int e = threadIdx.x; e < m * m; e += blockDim.x) {
-      const int i = j + 1 + e / m, k = j + 1 + e % m;
-      if (k <= i) a[i * b + k] -= a[i * b + j] * a[k * b + j];
-    }
-    __syncthreads();
-  }
-  for (int e = threadIdx.x; e < b * b; e += blockDim.x) {
-    const int i = e / b, k = e % b;
-    A[(k0 + i) * n + k0 + k] = k <= i ? a[e] : 0.0;
-  }
-  // W = L^-1 by forward substitution, W[i][t] = -(sum_{t<=k<i} L[i][k] W[k][t]) / L[i][i] for
-  // t < i and W[i][i] = 1 / L[i][i]: thread t owns column t of W (written and re-read by that
-  // thread only), L comes from LDS.
-  const int t = threadIdx.x;
-  if (t < b) {
-    for (int i = 0; i < b; ++i) {
-      double v = 0.0;
-      if (t < i) {
-        double acc = 0.0;
-        for (int k = t; k < i; ++k) acc += a[i * b + k] * W[k * b + t];
-        v = -acc / a[i * b + i];
-      } else if (t == i) {
-        v = 1.0 / a[i * b + i];
+      const double p = sqrt(d), ip = 1.0 / p;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        ca[k] *= ip;
+        cb[k] *= ip;
+        xr[k] *= ip;
       }
-      W[i * b + t] = v;
+#pragma unroll
+      for (int a = o; a < 8; ++a)
+#pragma unroll
+        for (int c = o; c < 8; ++c) l[a][c] = fma(-ca[a], cb[c], l[a][c]);
+      if (tj == s)  // column j of L
+#pragma unroll
+        for (int a = 0; a < 8; ++a) l[a][o] = ti + 16 * a == j ? p : ca[a];
+      if (ti == s) ca[o] = -1.0;  // row j of x: 0 - (-1) (row / p)
+#pragma unroll
+      for (int a = o; a < 8; ++a)
+#pragma unroll
+        for (int c = 0; c <= o; ++c) x[a][c] = fma(-ca[a], xr[c], x[a][c]);
     }
   }
+#pragma unroll
+  for (int a = 0; a < 8; ++a)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int i = ti + 16 * a, j = tj + 16 * c;
+      if (i < b && j < b) {
+        L[(k0 + i) * n + k0 + j] = j <= i ? l[a][c] : 0.0;
+        W[i * b + j] = Linv[(k0 + i) * n + k0 + j] = j <= i ? x[a][c] : 0.0;
+      }
+    }
 }
 
-// Zero the strict upper triangle of the n x n row-major A.
-__global__ void k_zero_upper(double* A, int64_t n) {
-  const int64_t nn = n * n;
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < nn; e += (int64_t)gridDim.x * 256)
-    if (e % n > e / n) A[e] = 0.0;
+__global__ void k_zero(double* A, int64_t n) {
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256)
+    A[e] = 0.0;
 }
 
 __global__ void k_nonfinite(const double* A, int64_t n, int* bad) {
@@ -255,63 +308,82 @@ __global__ void k_nonfinite(const double* A, int64_t n, int* bad) {
   if (f) atomicOr(bad, 1);
 }
 
+// A = -A, with the check of k_nonfinite
+__global__ void k_negate(double* A, int64_t n, int* bad) {
+  int f = 0;
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
+    const double v = A[e];
+    if (!isfinite(v)) f = 1;
+    A[e] = -v;
+  }
+  if (f) atomicOr(bad, 1);
+}
+
+dim3 ew_grid(int64_t n) {
+  const int64_t b = (n + 255) / 256;
+  return dim3((unsigned)(b < 1 ? 1 : b > 8192 ? 8192 : b));
+}
+
+// C = alpha A B + beta X (X nullable) in FP64, small tiles.
+hipError_t product(int M, int N, int K, const double* A, int64_t lda, int la, const double* B, int64_t ldb,
+                   int lb, double* C, int64_t ldc, double alpha, const double* X, double beta, int tri,
+                   int kcut, hipStream_t s) {
+  GemmDesc d{CF64, T_F64, T_F64, T_F64, T_F64, la, lb, 0, 1};
+  GemmOp op{};
+  op.M = M; op.N = N; op.nseg = 1;
+  op.A[0] = A; op.lda[0] = lda;
+  op.B[0] = B; op.ldb[0] = ldb;
+  op.K[0] = K;
+  op.C = C; op.ldc = ldc;
+  op.X = X; op.ldx = X ? ldc : 0;
+  op.alpha = alpha; op.beta = beta;
+  op.tri = tri;
+  op.kcut = kcut;
+  direct_choose(d, &op, 1);
+  return gemm_launch(d, &op, 1, nullptr, nullptr, 0, s);
+}
+
+hipError_t read_flag(const int* flag, hipStream_t s, int* out) {
+  const hipError_t e = hipMemcpyAsync(out, flag, sizeof(int), hipMemcpyDeviceToHost, s);
+  return e != hipSuccess ? e : hipStreamSynchronize(s);
+}
+
 }  // namespace
 
+#define TRYHIP(x)                          \
+  do {                                     \
+    const hipError_t e_ = (x);             \
+    if (e_ != hipSuccess) return e_;       \
+  } while (0)
+
 size_t invert_work_doubles(int64_t n) {
-  // U (n x NB), R (NB x n), W (NB x NB), flag word
+  // U, V (n x NB), W (NB x NB), flag word
   return (size_t)n * NB * 2 + (size_t)NB * NB + 8;
 }
 
-hipError_t invert_in_place(double* A, int64_t n, double* work, hipStream_t s, int* bad_host) {
+hipError_t invert_symmetric(double* A, int64_t n, double* work, hipStream_t s, int* bad_host) {
   double* U = work;
-  double* R = U + (size_t)n * NB;
-  double* W = R + (size_t)n * NB;
+  double* V = U + (size_t)n * NB;
+  double* W = V + (size_t)n * NB;
   int* flag = reinterpret_cast<int*>(W + (size_t)NB * NB);
-  hipError_t e = hipMemsetAsync(flag, 0, sizeof(int), s);
-  if (e != hipSuccess) return e;
+  const int N = (int)n;
+  TRYHIP(hipMemsetAsync(flag, 0, sizeof(int), s));
   for (int64_t k0 = 0; k0 < n; k0 += NB) {
     const int b = (int)((n - k0) < NB ? (n - k0) : NB);
-    int64_t total = n * b;
-    int blocks = (int)((total + 255) / 256);
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_panel, dim3(blocks), dim3(256), 0, s, A, n, k0, b, U, W);
-    hipLaunchKernelGGL(k_small_gj, dim3(1), dim3(1024), 0, s, W, b, flag);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // R = W * A[k0:k0+b, :]   (b x n, K = b)
-    GemmDesc d{CF64, T_F64, T_F64, T_F64, T_F64, KC, RC, 1, 1};
-    GemmOp op{};
-    op.M = b; op.N = (int)n; op.nseg = 1;
-    op.A[0] = W; op.lda[0] = b;
-    op.B[0] = A + k0 * n; op.ldb[0] = n;
-    op.K[0] = b;
-    op.C = R; op.ldc = n;
-    op.X = nullptr; op.ldx = 0;
-    op.alpha = 1.0; op.beta = 0.0;
-    if ((e = gemm_launch(d, &op, 1, nullptr, nullptr, 0, s)) != hipSuccess) return e;
-    // A = A - U R   (n x n, K = b), in place; 128 x 128 tiles at two workgroups per CU (this
-    // update streams the whole matrix once per pivot block: 0.27 against 0.36 s for the
-    // 13000-orbital inverse with one workgroup per CU)
-    GemmDesc d2{CF64, T_F64, T_F64, T_F64, T_F64, KC, RC, 4, 1};
-    GemmOp op2{};
-    op2.M = (int)n; op2.N = (int)n; op2.nseg = 1;
-    op2.A[0] = U; op2.lda[0] = b;
-    op2.B[0] = R; op2.ldb[0] = n;
-    op2.K[0] = b;
-    op2.C = A; op2.ldc = n;
-    op2.X = A; op2.ldx = n;
-    op2.alpha = -1.0; op2.beta = 1.0;
-    if ((e = gemm_launch(d2, &op2, 1, nullptr, nullptr, 0, s)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_panel, ew_grid(n * b), dim3(256), 0, s, A, n, k0, b, U, W);
+    hipLaunchKernelGGL(k_small_gj, dim3(1), dim3(256), 0, s, W, b, flag);
+    TRYHIP(hipGetLastError());
+    if (n > b) {
+      TRYHIP(product(N, b, b, U, b, KC, W, b, RC, V, b, 1.0, nullptr, 0.0, 0, 0, s));    // V = U W
+      TRYHIP(product(N, N, b, V, b, KC, U, b, KC, A, n, -1.0, A, 1.0, 1, 0, s));  // A -= V U^T
+    }
+    hipLaunchKernelGGL(k_sweep_write, dim3((unsigned)((n + 31) / 32), (b + 31) / 32), dim3(256), 0, s, A,
+                       n, k0, b, V, W);
+    TRYHIP(hipGetLastError());
   }
-  const int64_t nn = n * n;
-  int blocks = (int)((nn + 255) / 256);
-  if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(k_nonfinite, dim3(blocks), dim3(256), 0, s, A, nn, flag);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  int h = 0;
-  if ((e = hipMemcpyAsync(&h, flag, sizeof(int), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-  if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-  *bad_host = h;
-  return hipSuccess;
+  hipLaunchKernelGGL(k_negate, ew_grid(n * n), dim3(256), 0, s, A, n * n, flag);
+  TRYHIP(hipGetLastError());
+  return read_flag(flag, s, bad_host);
 }
 
 size_t inverse_residual_work_doubles(int64_t n) { return (size_t)3 * PROBES * n + 8; }
@@ -332,27 +404,13 @@ hipError_t inverse_residual(const double* P, const double* S, const double* T, d
   hipLaunchKernelGGL(k_probe, dim3(blocks), dim3(256), 0, s, X, n, PROBES);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  GemmDesc d{CF64, T_F64, T_F64, T_F64, T_F64, KC, KC, 0, 1};
-  auto op_of = [&](const double* A, const double* B, double* C, const double* Xa, double alpha,
-                   double beta) {
-    GemmOp op{};
-    op.M = PROBES; op.N = (int)n; op.nseg = 1;
-    op.A[0] = A; op.lda[0] = n;
-    op.B[0] = B; op.ldb[0] = n;
-    op.K[0] = (int)n;
-    op.C = C; op.ldc = n;
-    op.X = Xa; op.ldx = Xa ? n : 0;
-    op.alpha = alpha; op.beta = beta;
-    return op;
+  const int N = (int)n;
+  auto mul = [&](const double* A, const double* B, double* C, const double* Xa, double alpha, double beta) {
+    return product(PROBES, N, N, A, n, KC, B, n, KC, C, n, alpha, Xa, beta, 0, 0, s);
   };
-  GemmOp o1 = op_of(X, P, Y, nullptr, 1.0, 0.0);  // Y = X P
-  if ((e = gemm_launch(d, &o1, 1, nullptr, nullptr, 0, s)) != hipSuccess) return e;
-  GemmOp o2 = op_of(Y, S, Z, X, 1.0, -1.0);  // Z = Y S - X
-  if ((e = gemm_launch(d, &o2, 1, nullptr, nullptr, 0, s)) != hipSuccess) return e;
-  if (T) {
-    GemmOp o3 = op_of(Y, T, Z, Z, inv_tau, 1.0);  // Z += (1/tau) Y T
-    if ((e = gemm_launch(d, &o3, 1, nullptr, nullptr, 0, s)) != hipSuccess) return e;
-  }
+  TRYHIP(mul(X, P, Y, nullptr, 1.0, 0.0));       // Y = X P
+  TRYHIP(mul(Y, S, Z, X, 1.0, -1.0));            // Z = Y S - X
+  if (T) TRYHIP(mul(Y, T, Z, Z, inv_tau, 1.0));  // Z += (1/tau) Y T
   hipLaunchKernelGGL(k_maxabs, dim3(1), dim3(1024), 0, s, Z, total, out);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = hipMemcpyAsync(res_host, out, sizeof(double), hipMemcpyDeviceToHost, s)) != hipSuccess)
@@ -360,57 +418,42 @@ hipError_t inverse_residual(const double* P, const double* S, const double* T, d
   return hipStreamSynchronize(s);
 }
 
-size_t cholesky_work_doubles() { return (size_t)NB * NB + 8; }
+size_t cholesky_work_doubles(int64_t n) { return (size_t)n * NB + (size_t)NB * NB + 8; }
 
-// Blocked right-looking Cholesky S = L L^T in place on A (n x n, row-major, symmetric positive
-// definite): for each block column K (width b <= 128), factor A_KK and invert its triangle in one
-// workgroup (W), L_IK = A_IK W^T for the rows below (one 128-wide GEMM tile per row block, so
-// the in-place update reads each row block before writing it), then A_II -= L_IK L_IK^T on the
-// whole trailing square (GEMM). The strict upper triangle is zeroed at the end.
-hipError_t cholesky_in_place(double* A, int64_t n, double* work, hipStream_t s, int* bad_host) {
-  double* W = work;
+// S = L L^T and L^-1, both lower with zeros above (n x n, row-major), from A = S, which is overwritten.
+// For each block column K (width b <= 128): factor A_KK and invert its triangle in one workgroup
+// (W = L_KK^-1), L_IK = A_IK W^T for the rows below, A_II -= L_IK L_IK^T on the trailing square
+// (upper half, mirrored), and row block K of the inverse from those above it,
+// L^-1_K = -W (L_K,<K L^-1_<K), whose inner product skips the zeros of L^-1.
+hipError_t cholesky_and_inverse(double* A, double* L, double* Linv, int64_t n, double* work, hipStream_t s,
+                                int* bad_host) {
+  double* T = work;  // b x k0
+  double* W = T + (size_t)n * NB;
   int* flag = reinterpret_cast<int*>(W + (size_t)NB * NB);
-  hipError_t e = hipMemsetAsync(flag, 0, sizeof(int), s);
-  if (e != hipSuccess) return e;
+  TRYHIP(hipMemsetAsync(flag, 0, sizeof(int), s));
+  hipLaunchKernelGGL(k_zero, ew_grid(n * n), dim3(256), 0, s, L, n * n);
+  hipLaunchKernelGGL(k_zero, ew_grid(n * n), dim3(256), 0, s, Linv, n * n);
   for (int64_t k0 = 0; k0 < n; k0 += NB) {
     const int b = (int)((n - k0) < NB ? (n - k0) : NB);
-    hipLaunchKernelGGL(k_chol_block, dim3(1), dim3(1024), 0, s, A, n, k0, b, W, flag);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int64_t r0 = k0 + b, R = n - r0;
+    hipLaunchKernelGGL(k_chol_block, dim3(1), dim3(256), 0, s, A, L, Linv, n, k0, b, W, flag);
+    TRYHIP(hipGetLastError());
+    if (k0 > 0) {
+      const int K = (int)k0;
+      TRYHIP(product(b, K, K, L + k0 * n, n, KC, Linv, n, RC, T, K, 1.0, nullptr, 0.0, 0, KCUT_B_FROM_N, s));
+      TRYHIP(product(b, K, b, W, b, KC, T, K, RC, Linv + k0 * n, n, -1.0, nullptr, 0.0, 0, 0, s));
+    }
+    const int64_t r0 = k0 + b;
+    const int R = (int)(n - r0);
     if (R <= 0) break;
-    double* panel = A + r0 * n + k0;
-    // L_IK = A_IK W^T: 128 x 128 tiles, one tile across the b columns (in place)
-    GemmDesc d{CF64, T_F64, T_F64, T_F64, T_F64, KC, KC, 0, 1};
-    GemmOp op{};
-    op.M = (int)R; op.N = b; op.nseg = 1;
-    op.A[0] = panel; op.lda[0] = n;
-    op.B[0] = W; op.ldb[0] = b;
-    op.K[0] = b;
-    op.C = panel; op.ldc = n;
-    op.alpha = 1.0; op.beta = 0.0;
-    if ((e = gemm_launch(d, &op, 1, nullptr, nullptr, 0, s)) != hipSuccess) return e;
-    // A_II -= L_IK L_IK^T (trailing square, in place)
-    GemmOp op2{};
-    op2.M = (int)R; op2.N = (int)R; op2.nseg = 1;
-    op2.A[0] = panel; op2.lda[0] = n;
-    op2.B[0] = panel; op2.ldb[0] = n;
-    op2.K[0] = b;
-    op2.C = A + r0 * n + r0; op2.ldc = n;
-    op2.X = A + r0 * n + r0; op2.ldx = n;
-    op2.alpha = -1.0; op2.beta = 1.0;
-    if ((e = gemm_launch(d, &op2, 1, nullptr, nullptr, 0, s)) != hipSuccess) return e;
+    double* LI = L + r0 * n + k0;
+    double* AI = A + r0 * n + r0;
+    TRYHIP(product(R, b, b, A + r0 * n + k0, n, KC, W, b, KC, LI, n, 1.0, nullptr, 0.0, 0, 0, s));
+    TRYHIP(product(R, R, b, LI, n, KC, LI, n, KC, AI, n, -1.0, AI, 1.0, 1, 0, s));
   }
-  const int64_t nn = n * n;
-  int blocks = (int)((nn + 255) / 256);
-  if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(k_zero_upper, dim3(blocks), dim3(256), 0, s, A, n);
-  hipLaunchKernelGGL(k_nonfinite, dim3(blocks), dim3(256), 0, s, A, nn, flag);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  int h = 0;
-  if ((e = hipMemcpyAsync(&h, flag, sizeof(int), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-  if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-  *bad_host = h;
-  return hipSuccess;
+  hipLaunchKernelGGL(k_nonfinite, ew_grid(n * n), dim3(256), 0, s, L, n * n, flag);
+  hipLaunchKernelGGL(k_nonfinite, ew_grid(n * n), dim3(256), 0, s, Linv, n * n, flag);
+  TRYHIP(hipGetLastError());
+  return read_flag(flag, s, bad_host);
 }
 
 }  // namespace omm
