@@ -250,7 +250,10 @@ hipError_t launch_products(const GemmDesc& d, const GemmOp* ops, int nops, const
   const int splitk = dd.splitk > 1 ? dd.splitk : 1;
   if (splitk > 1 && (!ws || ws_bytes < gemm_splitk_ws_bytes(ops, nops, splitk)))
     return hipErrorInvalidValue;
-  dim3 grid(8 * per, splitk, nops);
+  // small tiles of symmetric or triangular products are dealt in runs: whole rounds of 8 XCDs x 16
+  bool dealt = false;
+  for (int i = 0; i < nops; ++i) dealt |= ops[i].tri || ops[i].kcut;
+  dim3 grid(tile_direct(dd.tile) && dealt ? (tiles + 127) / 128 * 128 : 8 * per, splitk, nops);
   hipLaunchKernelGGL(fn, grid, dim3(tile_threads(dd.tile, dd.compute)), 0, s, b, done, splitk, ws);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splitk == 1) return e;
