@@ -91,7 +91,8 @@ struct omm_ctx {
   size_t ws_bytes = 0;
   DevState* st = nullptr;
   DevState* st_host = nullptr;  // pinned
-  int* flags = nullptr;
+  int* flags = nullptr;       // 8 device ints for the checks of new inputs
+  int* flags_host = nullptr;  // pinned copy
   double* trace = nullptr;
   int trace_cap = 0;
   double* nn_scratch = nullptr;  // N x N FP64 (density / EDM / preconditioner work)
@@ -1464,6 +1465,7 @@ int omm_destroy(omm_ctx* c) {
     dfree(c->kl_idx[i]);
   }
   if (c->st_host) (void)hipHostFree(c->st_host);
+  if (c->flags_host) (void)hipHostFree(c->flags_host);
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   if (c->own) (void)hipStreamDestroy(c->own);
   delete c;
@@ -1542,11 +1544,10 @@ int omm_set_stream(omm_ctx* c, void* s) {
   return OMM_OK;
 }
 
-// Copies the symmetrized S and T in from `src_S`, `src_T` (device, or host through the Hs
-// buffer as staging: Hs is rebuilt from H and S before it is read again) and reports whether
-// either changed bit for bit; with no earlier S and T (or T added or dropped) they count as
-// changed.
-int load_S_T(omm_ctx* c, const double* src_S, const double* src_T, bool host, bool* changed) {
+// Copies the symmetrized S and T in from host memory, through the Hs buffer as staging (Hs is
+// rebuilt from H and S before it is read again), and reports whether either changed bit for bit;
+// with no earlier S and T (or T added or dropped) they count as changed.
+int load_S_T(omm_ctx* c, const double* src_S, const double* src_T, bool* changed) {
   const int64_t n = c->N;
   const size_t nn = (size_t)n * n, bytes = nn * sizeof(double);
   const bool compare = c->have_HS && (src_T != nullptr) == c->have_T;
@@ -1556,45 +1557,48 @@ int load_S_T(omm_ctx* c, const double* src_S, const double* src_T, bool host, bo
   TRY(dalloc(c, &c->Hs, nn));
   c->hs_valid = false;
   int diff = compare ? 0 : 1;
-  HIPCHK(c, hipMemcpyAsync(c->flags + 2, &diff, sizeof(int), hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipMemcpyAsync(c->flags + 6, &diff, sizeof(int), hipMemcpyHostToDevice, c->stream));
   double* dsts[2] = {c->S, c->T};
   const double* srcs[2] = {src_S, src_T};
   for (int k = 0; k < 2; ++k) {
     if (!srcs[k]) continue;
     // staged and symmetrized first, so that the stored copy is compared with what would be stored
-    HIPCHK(c, hipMemcpyAsync(c->Hs, srcs[k], bytes,
-                             host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->Hs, srcs[k], bytes, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, symmetrize(c->Hs, n, c->stream));
-    HIPCHK(c, copy_compare_f64(c->Hs, dsts[k], (int64_t)nn, c->flags + 2, c->stream));
+    HIPCHK(c, copy_compare_f64(c->Hs, dsts[k], (int64_t)nn, c->flags + 6, c->stream));
   }
-  HIPCHK(c, hipMemcpyAsync(&diff, c->flags + 2, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(c, hipMemcpyAsync(&diff, c->flags + 6, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   *changed = diff != 0;
   return OMM_OK;
 }
 
-// S and T (compared with the stored copies), then H, from host or device memory. On failure the
-// inputs count as absent and everything derived from them is dropped.
-int load_inputs(omm_ctx* c, const double* H, const double* S, const double* T, bool host) {
+// The new inputs are in (r == OMM_OK), or none is: on a failure the inputs count as absent and
+// everything derived from them is dropped.
+int loaded(omm_ctx* c, int r, bool have_T, bool st_changed) {
+  if (r != OMM_OK) {
+    c->have_HS = false;
+    invalidate(c, true);
+    return r;
+  }
+  c->have_T = have_T;
+  c->have_HS = true;
+  invalidate(c, st_changed);
+  return OMM_OK;
+}
+
+// S and T (compared with the stored copies), then H, from host memory.
+int load_inputs(omm_ctx* c, const double* H, const double* S, const double* T) {
   const size_t bytes = (size_t)c->N * c->N * sizeof(double);
   bool st_changed = true;
-  int r = load_S_T(c, S, T, host, &st_changed);
+  int r = load_S_T(c, S, T, &st_changed);
   if (r == OMM_OK) {
-    const hipError_t e0 = hipMemcpyAsync(c->H, H, bytes,
-                                         host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
-                                         c->stream);
+    const hipError_t e0 = hipMemcpyAsync(c->H, H, bytes, hipMemcpyHostToDevice, c->stream);
     const hipError_t e1 = e0 == hipSuccess ? symmetrize(c->H, c->N, c->stream) : e0;
     const hipError_t e2 = e1 == hipSuccess ? hipStreamSynchronize(c->stream) : e1;
     if (e2 != hipSuccess) r = fail(c, OMM_E_HIP, std::string("copying H: ") + hipGetErrorString(e2));
   }
-  if (r != OMM_OK) {
-    invalidate(c, true);
-    return r;
-  }
-  c->have_T = T != nullptr;
-  c->have_HS = true;
-  invalidate(c, st_changed);
-  return OMM_OK;
+  return loaded(c, r, T != nullptr, st_changed);
 }
 
 int omm_set_HS(omm_ctx* c, const double* H, const double* S, const double* T) {
@@ -1614,7 +1618,7 @@ int omm_set_HS(omm_ctx* c, const double* H, const double* S, const double* T) {
   TRY(ensure_inputs(c));
   // Validated to 1e-10; store exactly symmetric copies so that every operator product may read
   // rows in place of columns.
-  return load_inputs(c, H, S, T, true);
+  return load_inputs(c, H, S, T);
 }
 
 int omm_set_HS_device(omm_ctx* c, const double* dH, const double* dS, const double* dT) {
@@ -1622,20 +1626,34 @@ int omm_set_HS_device(omm_ctx* c, const double* dH, const double* dS, const doub
   if (!dH || !dS) return fail(c, OMM_E_ARG, "H and S are required");
   const int64_t n = c->N;
   TRY(ensure_inputs(c));
+  if (dT) TRY(dalloc(c, &c->T, (size_t)n * n));
   TRY(dalloc(c, &c->flags, 8));
-  const double* mats[3] = {dH, dS, dT};
+  if (!c->flags_host && hipHostMalloc((void**)&c->flags_host, 8 * sizeof(int), 0) != hipSuccess) {
+    c->flags_host = nullptr;
+    return fail(c, OMM_E_ALLOC, "hipHostMalloc failed");
+  }
+  // One pass that checks all three inputs and compares S and T with the stored copies (with no
+  // earlier ones, or T added or dropped, they count as changed), one round trip for its flags, and
+  // one pass that stores what changed: H, and S and T if either did.
+  const bool compare = c->have_HS && (dT != nullptr) == c->have_T;
+  SymInputs in{{dH, dS, dT}, {nullptr, compare ? c->S : nullptr, compare && dT ? c->T : nullptr},
+               {c->H, c->S, c->T}};
+  int* h = c->flags_host;
+  HIPCHK(c, hipMemsetAsync(c->flags, 0, 8 * sizeof(int), c->stream));
+  HIPCHK(c, check_inputs(in, n, 1e-10, c->flags, c->stream));
+  HIPCHK(c, hipMemcpyAsync(h, c->flags, 8 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(c, hipStreamSynchronize(c->stream));
   const char* names[3] = {"H", "S", "T"};
   for (int i = 0; i < 3; ++i) {
-    if (!mats[i]) continue;
-    int h[2] = {0, 0};
-    HIPCHK(c, hipMemsetAsync(c->flags, 0, 2 * sizeof(int), c->stream));
-    HIPCHK(c, validate_symmetric(mats[i], n, 1e-10, c->flags, c->stream));
-    HIPCHK(c, hipMemcpyAsync(h, c->flags, 2 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    if (h[0]) return fail(c, OMM_E_NONFINITE, std::string(names[i]) + " has a non-finite entry");
-    if (h[1]) return fail(c, OMM_E_ASYMMETRIC, std::string(names[i]) + " is not symmetric");
+    if (h[2 * i]) return fail(c, OMM_E_NONFINITE, std::string(names[i]) + " has a non-finite entry");
+    if (h[2 * i + 1]) return fail(c, OMM_E_ASYMMETRIC, std::string(names[i]) + " is not symmetric");
   }
-  return load_inputs(c, dH, dS, dT, false);
+  const bool st_changed = !compare || h[6] != 0;
+  if (!st_changed) in.src[1] = in.src[2] = nullptr;
+  hipError_t e = store_inputs(in, n, c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);  // the caller may reuse its buffers
+  const int r = e == hipSuccess ? OMM_OK : fail(c, OMM_E_HIP, std::string("storing the inputs: ") + hipGetErrorString(e));
+  return loaded(c, r, dT != nullptr, st_changed);
 }
 
 int omm_minimize(omm_ctx* c, const double* C0, double eta, double tau, double tol, int max_iter) {

@@ -148,6 +148,16 @@ hipError_t copy_f64(const double* src, double* dst, int64_t n, hipStream_t s);
 hipError_t copy_compare_f64(const double* src, double* dst, int64_t n, int* diff, hipStream_t s);
 hipError_t validate_symmetric(const double* A, int64_t n, double rtol, int* flags, hipStream_t s);
 hipError_t symmetrize(double* A, int64_t n, hipStream_t s);
+// New inputs H, S, T (n x n, device; a null src is skipped) of a context in one pass each.
+struct SymInputs {
+  const double* src[3];
+  const double* compare[3];  // stored copy to compare with (exactly symmetric), nullable
+  double* dst[3];            // where the symmetrized input goes (may be compare)
+};
+// flags[2 z] non-finite, flags[2 z + 1] asymmetric, flags[6] some input differs from its stored copy;
+// flags (7 ints) are set, never cleared.
+hipError_t check_inputs(const SymInputs& in, int64_t n, double rtol, int* flags, hipStream_t s);
+hipError_t store_inputs(const SymInputs& in, int64_t n, hipStream_t s);
 
 // Energy of (HW, SW): writes partials then finalizes into st (init = 1: first energy of a run).
 hipError_t energy_init(const double* HW, const double* SW, int M, double* partials, DevState* st,

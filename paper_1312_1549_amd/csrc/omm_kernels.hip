@@ -194,6 +194,70 @@ __global__ void k_validate(const double* A, int64_t n, double rtol, int* flags) 
   if (bad_s) atomicOr(&flags[1], 1);
 }
 
+// Up to three symmetric inputs (blockIdx.z) on their way into a context: the checks of k_validate
+// (flags[2 z] non-finite, flags[2 z + 1] asymmetric) and, for those with a stored copy, flags[6] = 1 when
+// the symmetrized input differs from it bit for bit. Reads each input once and the upper half of
+// each stored copy (exactly symmetric); writes nothing.
+__global__ __launch_bounds__(NT) void k_check_inputs(SymInputs in, int64_t n, double rtol, int* flags) {
+  __shared__ double t[32][33];
+  const int64_t bi = (int64_t)blockIdx.y * 32, bj = (int64_t)blockIdx.x * 32;
+  const double* A = in.src[blockIdx.z];
+  const double* P = in.compare[blockIdx.z];
+  if (bj < bi || !A) return;  // the upper block triangle (incl. diagonal blocks) covers every pair
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int r = ty; r < 32; r += 8) {
+    const int64_t i = bj + r, j = bi + tx;
+    t[r][tx] = (i < n && j < n) ? A[i * n + j] : 0.0;
+  }
+  __syncthreads();
+  bool bad_f = false, bad_s = false, changed = false;
+  for (int r = ty; r < 32; r += 8) {
+    const int64_t i = bi + r, j = bj + tx;
+    if (i >= n || j >= n) continue;
+    const double a = A[i * n + j], b = t[tx][r];
+    bad_f |= !isfinite(a) || !isfinite(b);
+    bad_s |= !(fabs(a - b) <= rtol * fmax(1.0, fmax(fabs(a), fabs(b))));
+    if (P && j >= i)
+      changed |= __double_as_longlong(0.5 * (a + b)) != __double_as_longlong(P[i * n + j]);
+  }
+  // one relaxed store a wave (an atomic from every wave would queue on the address)
+  auto raise = [&](bool c, int* f) {
+    if (__any(c) && (threadIdx.x & 63) == 0)
+      __hip_atomic_store(f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  raise(bad_f, flags + 2 * blockIdx.z);
+  raise(bad_s, flags + 2 * blockIdx.z + 1);
+  raise(changed, flags + 6);
+}
+
+// dst = (src + src^T) / 2 of up to three inputs (blockIdx.z), each pair of elements from one load.
+__global__ __launch_bounds__(NT) void k_store_inputs(SymInputs in, int64_t n) {
+  __shared__ double t[32][33], u[32][33];
+  const int64_t bi = (int64_t)blockIdx.y * 32, bj = (int64_t)blockIdx.x * 32;
+  const double* A = in.src[blockIdx.z];
+  double* D = in.dst[blockIdx.z];
+  if (bj < bi || !A) return;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int r = ty; r < 32; r += 8) {
+    const int64_t i = bj + r, j = bi + tx;
+    t[r][tx] = (i < n && j < n) ? A[i * n + j] : 0.0;
+  }
+  __syncthreads();
+  for (int r = ty; r < 32; r += 8) {
+    const int64_t i = bi + r, j = bj + tx;
+    if (i >= n || j >= n) continue;
+    const double v = 0.5 * (A[i * n + j] + t[tx][r]);
+    D[i * n + j] = v;
+    u[r][tx] = v;
+  }
+  if (bi == bj) return;  // a diagonal block holds both halves
+  __syncthreads();
+  for (int r = ty; r < 32; r += 8) {
+    const int64_t i = bj + r, j = bi + tx;
+    if (i < n && j < n) D[i * n + j] = u[tx][r];
+  }
+}
+
 // A <- (A + A^T) / 2; one thread per unordered pair.
 __global__ void k_symmetrize(double* A, int64_t n) {
   __shared__ double t[32][33];
@@ -1183,6 +1247,18 @@ hipError_t copy_f64(const double* src, double* dst, int64_t n, hipStream_t s) {
 hipError_t validate_symmetric(const double* A, int64_t n, double rtol, int* flags, hipStream_t s) {
   const int tb = (int)((n + 31) / 32);
   hipLaunchKernelGGL(k_validate, dim3(tb, tb), dim3(NT), 0, s, A, n, rtol, flags);
+  return hipGetLastError();
+}
+
+hipError_t check_inputs(const SymInputs& in, int64_t n, double rtol, int* flags, hipStream_t s) {
+  const int tb = (int)((n + 31) / 32);
+  hipLaunchKernelGGL(k_check_inputs, dim3(tb, tb, 3), dim3(NT), 0, s, in, n, rtol, flags);
+  return hipGetLastError();
+}
+
+hipError_t store_inputs(const SymInputs& in, int64_t n, hipStream_t s) {
+  const int tb = (int)((n + 31) / 32);
+  hipLaunchKernelGGL(k_store_inputs, dim3(tb, tb, 3), dim3(NT), 0, s, in, n);
   return hipGetLastError();
 }
 
