@@ -77,32 +77,39 @@ size_t gemm_ws_bytes(const GemmDesc& d, const GemmOp* ops, int nops) {
 int gemm_num_tiles() { return NTILES; }
 
 // Which small tile an FP64 / FP32 launch takes. A CU works on one tile's MFMAs at a time, so the
-// launch lasts about ceil(tiles / 256) times one tile, at the rate the tile's shape reaches: the
-// shape with the least of that wins (the larger on a tie: fewer operand bytes). Rates relative to
-// the MFMA peak, measured on products that fill the chip evenly (FP64: 384 x 2048 x 2048, 2000 x
-// 13000 x 13000; FP32: 768 x 4096 x 4096 twice in a launch): small tiles ask for more operand bytes
-// per flop, and below three tiles per CU the 32 x 32 one leaves its SIMDs waiting (66 us against 45
-// us with 48 x 48 for the four 384 x 384 x 2048 projections).
+// launch lasts about ceil(tiles / 256) rounds of one tile's MFMAs, at the rate the tile's shape
+// reaches, plus what a round exposes of its first loads and its sum over the waves (more for the
+// larger tiles, of which fewer share a CU); the least of that wins, the larger tile on a tie (fewer
+// operand bytes). Rates relative to 72 (FP64) and 154 (FP32) TFLOP/s and the exposed times are
+// measured. FP64 384 x 2048 x 2048 (rule / measured, us): 16x32 73 / 75, 32x32 55 / 55, 48x48 76 / 74,
+// 48x64 53 / 54, 64x64 68 / 66, 64x96 98 / 96; two FP32 768 x 4096 x 4096: 32x32 556 / 541, 48x64 460 /
+// 448, 64x64 454 / 439. 32 x 32 asks for the most operand bytes per flop that still pays: with fewer
+// than three such tiles per CU its SIMDs wait for them (the four 384 x 384 x 2048 projections take 52
+// us with it, 45 with 48 x 48), and in FP32 with long K too (0.62 at K = 4096; 32 grouped systems with
+// K of 256 to 1024 take 101 us with it, 105 to 135 with the others).
 void direct_choose(GemmDesc& d, const GemmOp* ops, int nops) {
   static const double rate64[NDIRECT] = {0.64, 0.85, 0.93, 0.90, 0.94, 0.97};
   static const double rate32[NDIRECT] = {0.45, 0.62, 0.75, 0.77, 0.78, 0.85};
-  const double* rate = d.compute == CF64 ? rate64 : rate32;
+  static const double exposed[NDIRECT] = {0.5, 0.6, 2.0, 3.0, 4.0, 6.0};  // us per round
+  const bool f64 = d.compute == CF64;
+  const double fma_us = (f64 ? 72e6 : 154e6) / 2 / 256;  // multiply-adds per CU and us
+  double kmax = 1.0;
+  auto k_of = [](const GemmOp& op) { return (double)op.K[0] + (op.nseg > 1 ? op.K[1] : 0); };
+  for (int o = 0; o < nops; ++o) kmax = std::max(kmax, k_of(ops[o]));
   double best = 0.0;
   for (int i = 0; i < NDIRECT; ++i) {
     const int bm = DIRECT_BM[i], bn = DIRECT_BN[i];
-    // tiles, weighted by their K relative to the longest one (grouped products differ)
-    double tiles = 0.0;
-    int kmax = 1;
-    for (int o = 0; o < nops; ++o) kmax = std::max(kmax, ops[o].K[0] + (ops[o].nseg > 1 ? ops[o].K[1] : 0));
+    double tiles = 0.0;  // weighted by K (the products of a grouped launch differ)
     for (int o = 0; o < nops; ++o) {
       const double tm = (ops[o].M + bm - 1) / bm, tn = (ops[o].N + bn - 1) / bn;
-      const double k = ops[o].K[0] + (ops[o].nseg > 1 ? ops[o].K[1] : 0);
       // a symmetric product computes the tiles that reach the diagonal
-      tiles += (ops[o].tri ? tm * tn / 2 + std::max(tm, tn) / 2 : tm * tn) * k / kmax;
+      tiles += (ops[o].tri ? tm * tn / 2 + std::max(tm, tn) / 2 : tm * tn) * k_of(ops[o]) / kmax;
     }
     const double rounds = ceil(tiles / 256.0);
-    const double r = i == 1 && rounds < 3 ? 0.75 * rate[i] : rate[i];
-    const double cost = rounds * bm * bn / r;
+    double rate = f64 ? rate64[i] : rate32[i];
+    if (i == 1 && rounds < 3) rate *= 0.75;
+    else if (i == 1 && !f64 && kmax <= 1024) rate = 0.75;
+    const double cost = rounds * (bm * bn * kmax / (rate * fma_us) + exposed[i]);
     if (i == 0 || cost <= best) {
       best = cost;
       d.tile = DIRECT_TILE0 + i;
@@ -161,8 +168,7 @@ hipError_t gemm_grouped_launch(const GemmDesc& d, const GemmOp* d_ops, const int
   grouped_fn fn = d.compute == CF64 ? pick_grouped_f64(d) : pick_grouped_f32(d);
   if (!fn) return hipErrorInvalidValue;
   GroupedArgs g{d_ops, d_tile_start, d_done, nops};
-  // whole rounds of 8 XCDs x 16 tiles
-  hipLaunchKernelGGL(fn, dim3((tiles + 127) / 128 * 128), dim3(tile_threads(d.tile, d.compute)), 0,
+  hipLaunchKernelGGL(fn, dim3(deal_grid(tiles)), dim3(tile_threads(d.tile, d.compute)), 0,
                      s, g);
   return hipGetLastError();
 }
@@ -250,10 +256,10 @@ hipError_t launch_products(const GemmDesc& d, const GemmOp* ops, int nops, const
   const int splitk = dd.splitk > 1 ? dd.splitk : 1;
   if (splitk > 1 && (!ws || ws_bytes < gemm_splitk_ws_bytes(ops, nops, splitk)))
     return hipErrorInvalidValue;
-  // small tiles of symmetric or triangular products are dealt in runs: whole rounds of 8 XCDs x 16
+  // small tiles of symmetric or triangular products are dealt in short runs
   bool dealt = false;
   for (int i = 0; i < nops; ++i) dealt |= ops[i].tri || ops[i].kcut;
-  dim3 grid(tile_direct(dd.tile) && dealt ? (tiles + 127) / 128 * 128 : 8 * per, splitk, nops);
+  dim3 grid(tile_direct(dd.tile) && dealt ? std::max(deal_grid(tiles), 8 * per) : 8 * per, splitk, nops);
   hipLaunchKernelGGL(fn, grid, dim3(tile_threads(dd.tile, dd.compute)), 0, s, b, done, splitk, ws);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splitk == 1) return e;

@@ -350,16 +350,15 @@ __device__ __forceinline__ void direct_tile(const GemmOp& op, int tm, int tn) {
   }
 }
 
-// Workgroup -> tile in runs of RUN consecutive tiles per XCD, dealt in turn.
-template <int RUN>
-__device__ __forceinline__ int dealt_tile(int bid) {
-  const int x = bid & 7, y = bid >> 3;
-  return (y / RUN) * (8 * RUN) + x * RUN + y % RUN;
+// Workgroup -> tile in runs of consecutive tiles per XCD, dealt in turn. The grid is whole rounds of 8
+// runs (deal_grid).
+__device__ __forceinline__ int dealt_tile(int bid, int total) {
+  const int run = deal_run(total), x = bid & 7, y = bid >> 3;
+  return (y / run) * (8 * run) + x * run + y % run;
 }
-constexpr int DIRECT_RUN = 16;
 
 // Up to 4 same-shape products (blockIdx.z). Each XCD gets one contiguous run of tiles, except where the
-// work of a tile depends on its place (symmetric results, triangular operands): there runs of 16
+// work of a tile depends on its place (symmetric results, triangular operands): there short runs
 // are dealt to the XCDs in turn, from the end with the long K ranges and the columns that reach
 // furthest above the diagonal (one run each left the last XCD with twice the average: 477 instead
 // of 296 us for a symmetric 4096 x 4096 x 768).
@@ -374,7 +373,7 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmBatch bat
   const int total = tiles_m * tiles_n, per = (total + 7) >> 3;
   int t;
   if (op.tri || op.kcut) {
-    t = dealt_tile<DIRECT_RUN>(blockIdx.x);
+    t = dealt_tile(blockIdx.x, total);
     if (!(op.kcut & KCUT_B_FROM_N)) t = total - 1 - t;
   } else {
     t = (int)(blockIdx.x >> 3) < per ? (blockIdx.x & 7) * per + (blockIdx.x >> 3) : total;
@@ -387,13 +386,14 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmBatch bat
 }
 
 // Products of uneven shapes: one workgroup per tile of the concatenated tile lists, dealt to the XCDs in
-// runs of 16. Tiles of a stopped system return at once.
+// short runs. Tiles of a stopped system return at once.
 template <int MODE, typename TA, typename TB, typename TC, typename TX, int LA, int LB, int TM,
           int TN, int NB, int OCC>
 __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_grouped(GroupedArgs g) {
   constexpr int BM = TM * 16, BN = TN * 16;
-  const int t = dealt_tile<DIRECT_RUN>(blockIdx.x);
-  if (t >= g.tile_start[g.nops]) return;
+  const int total = g.tile_start[g.nops];
+  const int t = dealt_tile(blockIdx.x, total);
+  if (t >= total) return;
   int lo = 0, hi = g.nops - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;

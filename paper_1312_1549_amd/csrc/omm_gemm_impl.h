@@ -1112,6 +1112,13 @@ constexpr int DIRECT_TILE0 = 7, NDIRECT = 6;
 constexpr int NTILES = DIRECT_TILE0 + NDIRECT;
 constexpr int DIRECT_BM[NDIRECT] = {16, 32, 48, 48, 64, 64};
 constexpr int DIRECT_BN[NDIRECT] = {32, 32, 48, 64, 64, 96};
+// Runs of consecutive tiles dealt to the XCDs in turn: 16 tiles share operand panels in an XCD's L2;
+// shorter where 8 runs of 16 would leave XCDs without tiles.
+__host__ __device__ inline int deal_run(int tiles) { return tiles >= 2048 ? 16 : tiles >= 128 ? tiles / 128 : 1; }
+inline int deal_grid(int tiles) {
+  const int r = 8 * deal_run(tiles);
+  return (tiles + r - 1) / r * r;
+}
 inline bool tile_direct(int t) { return t >= DIRECT_TILE0; }
 inline bool tile_big(int t, int mode) { return t >= 4 && is_bf16_mode(mode); }
 inline int tile_bm(int t, int mode) {
