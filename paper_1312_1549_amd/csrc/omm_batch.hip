@@ -309,7 +309,7 @@ int build_lists(omm_batch* b, bool f64) {
       D = s.D; HD = s.HD; SD = s.SD; Hs = s.Hs; S = s.S32; P = s.P;
     }
     // complex systems (real embeddings): every product follows C's row pairs and is computed
-    // for its first M / 2 rows (group_pair_rows fills the rest)
+    // for its first M / 2 rows, each stored with its pair rotation
     const int Mo = b->cplx ? M / 2 : M;
     const int* dn = &b->st[i].done;
     L.init1.ops.push_back(gop(Mo, N, N, C, N, Hs, N, HC, N));
@@ -344,22 +344,12 @@ int build_lists(omm_batch* b, bool f64) {
       L.proj.ops[k].tri = Mo == M;  // H'', S'' are symmetric
     for (int k = 0; k < 4; ++k) L.proj.done.push_back(dn);
   }
-  for (OpList* l : L.all()) BTRY(upload_list(b, *l));
-  BHIP(b, hipStreamSynchronize(b->stream));  // the uploads read host vectors
-  return OMM_OK;
-}
-
-// Complex batches: the second half of the rows of the products named by `which` (see
-// group_pair_rows).
-int fill_pairs(omm_batch* b, const SysDev* d_sys, int which, int parity, bool check_done) {
-  if (!b->cplx) return OMM_OK;
-  int mm = 0, mn = 0;
-  for (const BSys& s : b->sys) {
-    mm = std::max(mm, (int)s.M);
-    mn = std::max(mn, (int)s.N);
+  for (OpList* l : L.all()) {
+    if (b->cplx)
+      for (GemmOp& op : l->ops) op.pair_rows = op.M;
+    BTRY(upload_list(b, *l));
   }
-  BHIP(b, group_pair_rows(d_sys, (int)b->sys.size(), which, parity, check_done, mm, mn,
-                          b->stream));
+  BHIP(b, hipStreamSynchronize(b->stream));  // the uploads read host vectors
   return OMM_OK;
 }
 
@@ -368,14 +358,10 @@ int batch_iteration(omm_batch* b, PhaseLists& L, const SysDev* d_sys, int k) {
   const int n = (int)b->sys.size();
   const int p = k & 1;
   BTRY(launch_list(b, L.grad[p]));
-  BTRY(fill_pairs(b, d_sys, 2, p, true));
   BTRY(launch_list(b, L.pg[p]));
-  BTRY(fill_pairs(b, d_sys, 3, p, true));
   BHIP(b, group_direction(d_sys, n, p, k == 0 ? 1 : 0, b->stream));
   BTRY(launch_list(b, L.hdsd));
-  BTRY(fill_pairs(b, d_sys, 4, p, true));
   BTRY(launch_list(b, L.proj));
-  BTRY(fill_pairs(b, d_sys, 5, p, true));
   BHIP(b, group_line_search(d_sys, n, b->stream));
   BHIP(b, group_update(d_sys, n, b->stream));
   return OMM_OK;
@@ -404,11 +390,11 @@ int upload_sysdev(omm_batch* b, bool f64) {
     if (f64)
       sd[i] = SysDev{s.C64, s.HC64, s.SC64, s.G0_64, s.G1_64, s.PG64, s.D64, s.HD64, s.SD64,
                      s.HW, s.SW, s.H1, s.S1, s.H2, s.S2, s.partials, b->st + i, s.trace, (int)s.M,
-                     (int)s.N, s.p_kind > 0 ? 1 : 0, b->cplx ? 1 : 0, 1};
+                     (int)s.N, s.p_kind > 0 ? 1 : 0, 1};
     else
       sd[i] = SysDev{s.C, s.HC, s.SC, s.G0, s.G1, s.PG, s.D, s.HD, s.SD, s.HW, s.SW, s.H1, s.S1,
                      s.H2, s.S2, s.partials, b->st + i, s.trace, (int)s.M, (int)s.N,
-                     s.p_kind > 0 ? 1 : 0, b->cplx ? 1 : 0, 0};
+                     s.p_kind > 0 ? 1 : 0, 0};
   }
   BHIP(b, hipMemcpyAsync(f64 ? b->d_sys64 : b->d_sys, sd.data(), n * sizeof(SysDev),
                          hipMemcpyHostToDevice, b->stream));
@@ -434,9 +420,7 @@ int run_phase(omm_batch* b, bool f64, double tol, int max_iter) {
 
   // initial products and E_0 of every system
   BTRY(launch_list(b, L.init1));
-  BTRY(fill_pairs(b, d_sys, 0, 0, false));
   BTRY(launch_list(b, L.init2));
-  BTRY(fill_pairs(b, d_sys, 1, 0, false));
   BHIP(b, group_energy_init(d_sys, n, b->stream));
   BTRY(read_states(b));
   bool all_done = true;

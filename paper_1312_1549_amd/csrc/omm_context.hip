@@ -747,21 +747,13 @@ int split_state(omm_ctx* c, const T* HC, const T* SC, bool check_done = true) {
 
 // Complex problems on the real embedding: C = E(C_c) has row pairs [Re c, Im c], [-Im c, Re c],
 // and so does every product whose rows follow C's (E(X) E(Y) = E(X Y), E(X)^T = E(X^H)). Such a
-// product is computed for its first Mc rows and the other Mc filled by the pair rotation. Not
-// in the Cholesky flavour: the real Cholesky factor of E(S) is not an embedding, so C~ = C L has
-// no row pairs. Returns Mc, or 0 when every row is computed.
-int paired_rows(omm_ctx* c) { return c->cplx && !reduced(c) ? (int)c->Mc : 0; }
+// product is computed for its first Mc rows, each stored with its pair rotation (paired). Not in the
+// Cholesky flavour: the real Cholesky factor of E(S) is not an embedding, so C~ = C L has no row
+// pairs. Returns Mc, or 0 when every row is computed.
+int paired_rows(const omm_ctx* c) { return c->cplx && !reduced(c) ? (int)c->Mc : 0; }
 
-// The second half of the rows of a paired product X (rows x cols, row length ld; type FP64 or
-// FP32) and of its optional planes.
-int fill_pairs(omm_ctx* c, void* X, int type, int64_t ld, int64_t cols, const Plane* p,
-               bool check_done = true) {
-  const int rh = paired_rows(c);
-  if (!rh) return OMM_OK;
-  HIPCHK(c, pair_rows(X, type == T_F64, ld, p ? p->hi : nullptr, p ? p->lo : nullptr,
-                      p ? p->ld : 0, rh, (int)(cols / 2), check_done ? c->st : nullptr,
-                      c->stream));
-  return OMM_OK;
+void paired(const omm_ctx* c, GemmOp* ops, int nops) {
+  for (int i = 0; i < nops; ++i) ops[i].pair_rows = paired_rows(c);
 }
 
 // Initial products of a phase (Sec. 2.1, Eqs. 5-6; Sec. 2.3 footnote):
@@ -790,9 +782,8 @@ int initial_products(omm_ctx* c, Work<T>& w, int compute, const T* Hs, const T* 
   // reduced problem (S~ = I): SC = C, kept as its own copy, which every update then moves
   // exactly like C
   const bool sid = reduced(c);
+  paired(c, ops, 2);
   TRY(gemm(c, d, ops, sid ? 1 : 2, nullptr));
-  TRY(fill_pairs(c, w.HC, elem_type<T>(), N, N, nullptr, false));
-  if (!sid) TRY(fill_pairs(c, w.SC, elem_type<T>(), N, N, nullptr, false));
   if (sid)
     HIPCHK(c, hipMemcpyAsync(w.SC, w.C, mn * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
   if (bf) TRY(split_state(c, w.HC, w.SC, false));
@@ -801,9 +792,8 @@ int initial_products(omm_ctx* c, Work<T>& w, int compute, const T* Hs, const T* 
                     make_op2(Mo, M, N, bf ? pl(c->SC_p) : dn(w.SC, N), Cop, c->SW, M)};
   // C Hs C^T and C S C^T are symmetric (square products only: not with paired rows)
   if (!bf && Mo == M) ops2[0].tri = ops2[1].tri = 1;
+  paired(c, ops2, 2);
   TRY(gemm(c, d2, ops2, 2, nullptr));
-  TRY(fill_pairs(c, c->HW, T_F64, M, M, nullptr, false));
-  TRY(fill_pairs(c, c->SW, T_F64, M, M, nullptr, false));
   HIPCHK(c, energy_init(c->HW, c->SW, M, c->partials, c->st, trace, c->stream));
   return OMM_OK;
 }
@@ -893,8 +883,8 @@ int line_search_iteration(omm_ctx* c, Work<T>& w, int compute, const T* Hs, cons
       out_planes(op, c->G_p);
       if (!pg_split_enabled()) op.Clo = nullptr;
     }
+    paired(c, &op, 1);
     TRY(gemm(c, d, &op, 1, done));
-    TRY(fill_pairs(c, Gout, tg, N, N, fuse && c->p_kind > 0 ? &c->G_p : nullptr));
   }
   TRY(prof_mark(c));
   // BF16x3: the preconditioner is applied as its bf16 rounding P~ (the hi plane of P, a symmetric
@@ -919,8 +909,8 @@ int line_search_iteration(omm_ctx* c, Work<T>& w, int compute, const T* Hs, cons
     GemmDesc d{cP, ot, ot, tp, tp, KC, KC, 0, 1};
     GemmOp op = make_op2(Mo, N, N, bf ? pl(c->G_p) : dn(G, N), bf ? pl(c->P_p) : dn(P, N),
                          f32p ? (void*)w.PGf : (void*)w.PG, N);
+    paired(c, &op, 1);
     TRY(gemm(c, d, &op, 1, done));
-    TRY(fill_pairs(c, f32p ? (void*)w.PGf : (void*)w.PG, tp, N, N, nullptr));
     PG = w.PG;
   }
   TRY(prof_mark(c));
@@ -961,9 +951,8 @@ int line_search_iteration(omm_ctx* c, Work<T>& w, int compute, const T* Hs, cons
       out_planes(ops[0], c->HD_p);
       out_planes(ops[1], c->SD_p);
     }
+    paired(c, ops, 2);
     TRY(gemm(c, d, ops, sid ? 1 : 2, done));
-    TRY(fill_pairs(c, ops[0].C, td, N, N, fuse ? &c->HD_p : nullptr));
-    if (!sid) TRY(fill_pairs(c, ops[1].C, td, N, N, fuse ? &c->SD_p : nullptr));
   }
   TRY(prof_mark(c));
   if (bf && !fuse) {  // the projection stage's operand planes (D's lo plane stays zero)
@@ -985,8 +974,8 @@ int line_search_iteration(omm_ctx* c, Work<T>& w, int compute, const T* Hs, cons
     // H'' = D Hs D^T and S'' = D S D^T are symmetric (Eq. 15): their upper block triangles are
     // computed and mirrored (square products only: not with paired rows)
     if (Mo == M) ops[2].tri = ops[3].tri = 1;
+    paired(c, ops, 4);
     TRY(gemm(c, d, ops, 4, done));
-    for (double* X : {c->H1, c->S1, c->H2, c->S2}) TRY(fill_pairs(c, X, T_F64, M, M, nullptr));
   }
   TRY(prof_mark(c));
   HIPCHK(c, line_search(c->HW, c->SW, c->H1, c->S1, c->H2, c->S2, M, c->partials, c->st,
@@ -1156,18 +1145,16 @@ int resync_fp64(omm_ctx* c) {
       ops[i].kptr = c->kl_ptr[i];
       ops[i].kidx = c->kl_idx[i];
     }
+  paired(c, ops, 2);
   TRY(gemm(c, d, ops, sid ? 1 : 2, nullptr));
-  TRY(fill_pairs(c, w.HC, T_F64, N, N, nullptr, false));
-  if (!sid) TRY(fill_pairs(c, w.SC, T_F64, N, N, nullptr, false));
   if (sid)
     HIPCHK(c, hipMemcpyAsync(w.SC, w.C, (size_t)M * N * sizeof(double), hipMemcpyDeviceToDevice,
                              c->stream));
   GemmOp ops2[2] = {make_op(Mo, M, N, w.HC, N, w.C, N, c->HW, M),
                     make_op(Mo, M, N, w.SC, N, w.C, N, c->SW, M)};
   if (Mo == M) ops2[0].tri = ops2[1].tri = 1;  // symmetric
+  paired(c, ops2, 2);
   TRY(gemm(c, d, ops2, 2, nullptr));
-  TRY(fill_pairs(c, c->HW, T_F64, M, M, nullptr, false));
-  TRY(fill_pairs(c, c->SW, T_F64, M, M, nullptr, false));
   // the BF16x3 products read HC and SC through their planes
   TRY(split_state(c, w.HC, w.SC, false));
   const int it = c->st_host->iter;

@@ -73,6 +73,10 @@ struct GemmOp {
   // KCUT_* bits: known zeros of a triangular operand, skipped by the small tiles (one segment; the
   // others multiply them).
   int kcut;
+  // Paired result (real embedding of a complex product, N = 2 h columns, pair_rows = M rows
+  // computed; 0: none): row M + r is the pair rotation [-Im z, Re z] of row r = [Re z, Im z], stored
+  // with it (also in the planes).
+  int pair_rows;
 };
 // A(m, k) = 0 for k > m; B(n, k) = 0 for k > n; B(n, k) = 0 for k < n.
 enum KCut : int { KCUT_A_TO_M = 1, KCUT_B_TO_N = 2, KCUT_B_FROM_N = 4 };
@@ -137,11 +141,6 @@ hipError_t split_bf16_t(const float* src, unsigned short* hi, unsigned short* lo
                         int cols, int64_t ld, const DevState* st, hipStream_t s);
 hipError_t split_bf16_t(const double* src, unsigned short* hi, unsigned short* lo, int rows,
                         int cols, int64_t ld, const DevState* st, hipStream_t s);
-// Real embedding of a complex matrix with 2 rh rows and 2 h columns (row length ld): rows
-// rh .. 2 rh - 1 := [-X[r][h:2h], X[r][0:h]] of rows 0 .. rh - 1 (FP64 if f64, else FP32), and
-// the same for the optional bf16 planes hi/lo (row length ldp). Skipped when st->done.
-hipError_t pair_rows(void* X, bool f64, int64_t ld, unsigned short* hi, unsigned short* lo,
-                     int64_t ldp, int rh, int h, const DevState* st, hipStream_t s);
 hipError_t convert_f32_f64(const float* src, double* dst, int64_t n, hipStream_t s);
 hipError_t copy_f64(const double* src, double* dst, int64_t n, hipStream_t s);
 // dst = src, setting *diff to 1 when any element's bits change (*diff is not cleared)
@@ -216,7 +215,6 @@ struct SysDev {
   double* trace;                                   // max_iter + 2 entries
   int M, N;
   int precon;                                      // PG holds G P (else PG aliases G)
-  int paired;  // real embedding of a complex system: products computed for the first M / 2 rows
   int f64;     // type of the M x N arrays
 };
 constexpr int GROUP_BLOCKS = 64;
@@ -225,13 +223,6 @@ hipError_t group_energy_init(const SysDev* d_sys, int nsys, hipStream_t s);
 hipError_t group_direction(const SysDev* d_sys, int nsys, int parity, int first, hipStream_t s);
 hipError_t group_line_search(const SysDev* d_sys, int nsys, hipStream_t s);
 hipError_t group_update(const SysDev* d_sys, int nsys, hipStream_t s);
-// Rows M/2 .. M-1 of the paired systems' products from rows 0 .. M/2-1 by the pair rotation
-// (see pair_rows): which = 0 HC, SC; 1 HW, SW; 2 G of `parity`; 3 PG; 4 HD, SD; 5 H', S', H'',
-// S''. max_m, max_n bound the systems' sizes (grid shape); stopped systems are skipped when
-// check_done.
-hipError_t group_pair_rows(const SysDev* d_sys, int nsys, int which, int parity, bool check_done,
-                           int max_m, int max_n, hipStream_t s);
-
 // ---- preconditioner (omm_precon.hip) ----
 // In-place inverse of a symmetric n x n matrix by a blocked sweep; the result is exactly symmetric.
 // Returns hipSuccess and sets *bad (host) to 1 if a pivot block was singular or a non-finite value

@@ -854,29 +854,6 @@ __global__ __launch_bounds__(NT) void k_update_split_mn2(T* C, const unsigned sh
   }
 }
 
-// Real embedding of a complex matrix Z (rows 2 rh): row rh + r is the pair rotation of row r,
-// [-Im z, Re z] for [Re z, Im z] (each half h columns). Products whose rows follow the row pairs
-// of C are computed for the first rh rows; this fills the others, and the same rotation of the
-// optional bf16 planes (negation flips the sign bit: bf16 rounding is symmetric).
-template <typename T>
-__global__ void k_pair_rows(T* X, int64_t ld, unsigned short* hi, unsigned short* lo, int64_t ldp,
-                            int rh, int h, const DevState* st) {
-  if (st && st->done) return;
-  for (int64_t r = blockIdx.y; r < rh; r += gridDim.y)
-    for (int64_t c = (int64_t)blockIdx.x * NT + threadIdx.x; c < 2 * (int64_t)h;
-         c += (int64_t)gridDim.x * NT) {
-      const bool neg = c < h;
-      const int64_t src = neg ? c + h : c - h;
-      const T v = X[r * ld + src];
-      X[(r + rh) * ld + c] = neg ? -v : v;
-      if (hi) {
-        const unsigned short sgn = neg ? 0x8000 : 0;
-        hi[(r + rh) * ldp + c] = hi[r * ldp + src] ^ sgn;
-        lo[(r + rh) * ldp + c] = lo[r * ldp + src] ^ sgn;
-      }
-    }
-}
-
 // HW += x (H' + H'^T) + x^2 H'', SW likewise; partial sums of Tr HW, <SW, HW>, Tr SW.
 __device__ __forceinline__ void b_update_mm(double* HW, double* SW, const double* H1, const double* S1,
                             const double* H2, const double* S2, int M, double* partials,
@@ -1094,41 +1071,6 @@ __global__ void g_update_mn(const SysDev* sys) {
   if (d.f64) g_update_mn_t<double>(d);
   else g_update_mn_t<float>(d);
 }
-template <typename T>
-__device__ __forceinline__ void pair_fill(T* X, int rh, int h, int64_t r, int64_t c) {
-  const bool neg = c < h;
-  const T v = X[r * 2 * h + (neg ? c + h : c - h)];
-  X[(r + rh) * 2 * h + c] = neg ? -v : v;
-}
-
-__global__ void g_pair_rows(const SysDev* sys, int which, int parity, int check_done) {
-  const SysDev& d = sys[blockIdx.z];
-  if (!d.paired || (check_done && d.st->done)) return;
-  if (which == 3 && !d.precon) return;  // PG aliases G
-  const int rh = d.M / 2;
-  const bool mm = which == 1 || which == 5;  // M x M (FP64) or M x N (FP32 or FP64 state)
-  const int h = (mm ? d.M : d.N) / 2;
-  void* xs[2] = {nullptr, nullptr};  // M x N arrays of the state's type
-  double* xd[4] = {nullptr, nullptr, nullptr, nullptr};
-  if (which == 0) { xs[0] = d.HC; xs[1] = d.SC; }
-  if (which == 2) xs[0] = parity ? d.G1 : d.G0;
-  if (which == 3) xs[0] = d.PG;
-  if (which == 4) { xs[0] = d.HD; xs[1] = d.SD; }
-  if (which == 1) { xd[0] = d.HW; xd[1] = d.SW; }
-  if (which == 5) { xd[0] = d.H1; xd[1] = d.S1; xd[2] = d.H2; xd[3] = d.S2; }
-  for (int64_t r = blockIdx.y; r < rh; r += gridDim.y)
-    for (int64_t c = (int64_t)blockIdx.x * NT + threadIdx.x; c < 2 * (int64_t)h;
-         c += (int64_t)gridDim.x * NT) {
-      for (int a = 0; a < 2; ++a) {
-        if (!xs[a]) continue;
-        if (d.f64) pair_fill(static_cast<double*>(xs[a]), rh, h, r, c);
-        else pair_fill(static_cast<float*>(xs[a]), rh, h, r, c);
-      }
-      for (int a = 0; a < 4; ++a)
-        if (xd[a]) pair_fill(xd[a], rh, h, r, c);
-    }
-}
-
 __global__ void g_update_mm(const SysDev* sys) {
   const SysDev& d = sys[blockIdx.y];
   b_update_mm(d.HW, d.SW, d.H1, d.S1, d.H2, d.S2, d.M, d.partials, d.st, blockIdx.x, gridDim.x);
@@ -1198,20 +1140,6 @@ hipError_t split_bf16_t(const double* src, unsigned short* hi, unsigned short* l
   if (ld < rows) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_split_t<double>, dim3((cols + 31) / 32, (rows + 31) / 32), dim3(NT), 0, s,
                      src, hi, lo, rows, cols, ld, st);
-  return hipGetLastError();
-}
-
-hipError_t pair_rows(void* X, bool f64, int64_t ld, unsigned short* hi, unsigned short* lo,
-                     int64_t ldp, int rh, int h, const DevState* st, hipStream_t s) {
-  if (rh <= 0 || h <= 0) return hipSuccess;
-  if (ld < 2 * (int64_t)h || (hi && (!lo || ldp < 2 * (int64_t)h))) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((2 * (int64_t)h + NT - 1) / NT), (unsigned)(rh < 65535 ? rh : 65535));
-  if (f64)
-    hipLaunchKernelGGL(k_pair_rows<double>, grid, dim3(NT), 0, s, static_cast<double*>(X), ld, hi,
-                       lo, ldp, rh, h, st);
-  else
-    hipLaunchKernelGGL(k_pair_rows<float>, grid, dim3(NT), 0, s, static_cast<float*>(X), ld, hi, lo,
-                       ldp, rh, h, st);
   return hipGetLastError();
 }
 
@@ -1414,16 +1342,6 @@ hipError_t group_update(const SysDev* d_sys, int nsys, hipStream_t s) {
   hipLaunchKernelGGL(g_update_mn, dim3(4 * GROUP_BLOCKS, nsys), dim3(NT), 0, s, d_sys);
   hipLaunchKernelGGL(g_update_mm, dim3(GROUP_BLOCKS, nsys), dim3(NT), 0, s, d_sys);
   hipLaunchKernelGGL(g_update_final, dim3(1, nsys), dim3(NT), 0, s, d_sys);
-  return hipGetLastError();
-}
-
-hipError_t group_pair_rows(const SysDev* d_sys, int nsys, int which, int parity, bool check_done,
-                           int max_m, int max_n, hipStream_t s) {
-  if (nsys <= 0 || max_m < 2) return hipSuccess;
-  const int cols = (which == 1 || which == 5) ? max_m : max_n;
-  const dim3 grid((unsigned)((cols + NT - 1) / NT), (unsigned)std::min(max_m / 2, 4096),
-                  (unsigned)nsys);
-  hipLaunchKernelGGL(g_pair_rows, grid, dim3(NT), 0, s, d_sys, which, parity, check_done ? 1 : 0);
   return hipGetLastError();
 }
 
