@@ -21,6 +21,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/omm.h"
@@ -678,7 +679,7 @@ int alloc_common(omm_ctx* c) {
   TRY(dalloc(c, &c->S1, mm));
   TRY(dalloc(c, &c->H2, mm));
   TRY(dalloc(c, &c->S2, mm));
-  TRY(dalloc(c, &c->partials, (size_t)RED_BLOCKS * NCOEF));
+  TRY(dalloc(c, &c->partials, (size_t)RED_BLOCKS * (NCOEF + 3)));  // quartic's terms, energy's
   TRY(dalloc(c, &c->st, 1));
   if (!c->st_host) {
     if (hipHostMalloc((void**)&c->st_host, sizeof(DevState), 0) != hipSuccess) {
@@ -731,6 +732,12 @@ template <typename T>
 int split(omm_ctx* c, const T* src, Plane& p, int64_t rows, int64_t cols, bool check_done = true) {
   HIPCHK(c, split_bf16(src, p.hi, p.lo, rows, cols, p.ld, check_done ? c->st : nullptr, c->stream));
   return OMM_OK;
+}
+
+// Planes of HW, SW.
+int split_subspace(omm_ctx* c, bool check_done = true) {
+  TRY(split(c, c->HW, c->HW_p, c->M, c->M, check_done));
+  return split(c, c->SW, c->SW_p, c->M, c->M, check_done);
 }
 
 // Planes of HC, SC and of their transposes (after every change of HC, SC).
@@ -794,6 +801,7 @@ int initial_products(omm_ctx* c, Work<T>& w, int compute, const T* Hs, const T* 
   if (!bf && Mo == M) ops2[0].tri = ops2[1].tri = 1;
   paired(c, ops2, 2);
   TRY(gemm(c, d2, ops2, 2, nullptr));
+  if (bf) TRY(split_subspace(c, false));
   HIPCHK(c, energy_init(c->HW, c->SW, M, c->partials, c->st, trace, c->stream));
   return OMM_OK;
 }
@@ -863,10 +871,6 @@ int line_search_iteration(omm_ctx* c, Work<T>& w, int compute, const T* Hs, cons
   TRY(prof_mark(c));
   // G = 8 HC - 4 HW SC - 4 SW HC
   {
-    if (bf) {
-      TRY(split(c, c->HW, c->HW_p, M, M));
-      TRY(split(c, c->SW, c->SW_p, M, M));
-    }
     // BF16x3 reads the transposed planes of SC, HC (k-contiguous); the others read SC, HC by rows,
     // and HW, SW (symmetric) by columns, which needs no LDS (omm_gemm_direct.h)
     GemmDesc d{compute, bf ? T_BF16P : T_F64, ot, tg, et, bf ? KC : RC, bf ? KC : RC, 0, 1};
@@ -918,15 +922,15 @@ int line_search_iteration(omm_ctx* c, Work<T>& w, int compute, const T* Hs, cons
   // written only for the separate update
   T* Dcopy = fuse ? nullptr : w.D;
   if (f32p && c->p_kind > 0)
-    HIPCHK(c, (beta_and_direction<T, float, float>(Gf, w.PGf, Gfprev, Dcopy, mn, k == 0 ? 1 : 0,
+    HIPCHK(c, (beta_and_direction<T, float, float>(Gf, w.PGf, Gfprev, Dcopy, mn, k,
                                                   c->partials, c->st, c->stream, c->D_p.hi, N,
                                                   c->D_p.ld)));
   else if (f32p)  // no preconditioner: PG = G
-    HIPCHK(c, (beta_and_direction<T, float, float>(Gf, Gf, Gfprev, Dcopy, mn, k == 0 ? 1 : 0,
+    HIPCHK(c, (beta_and_direction<T, float, float>(Gf, Gf, Gfprev, Dcopy, mn, k,
                                                   c->partials, c->st, c->stream, c->D_p.hi, N,
                                                   c->D_p.ld)));
   else
-    HIPCHK(c, beta_and_direction<T>(G, PG, Gprev, Dcopy, mn, k == 0 ? 1 : 0, c->partials, c->st,
+    HIPCHK(c, beta_and_direction<T>(G, PG, Gprev, Dcopy, mn, k, c->partials, c->st,
                                     c->stream, bf ? c->D_p.hi : nullptr, N, c->D_p.ld));
   TRY(prof_mark(c));
   const Opnd Dop = bf ? pl(c->D_p) : dn(w.D, N);
@@ -972,35 +976,46 @@ int line_search_iteration(omm_ctx* c, Work<T>& w, int compute, const T* Hs, cons
                      make_op2(Mo, M, N, Dop, bf ? pl(c->HD_p) : dn(w.HD, N), c->H2, M),
                      make_op2(Mo, M, N, Dop, bf ? pl(SD_p) : dn(SD, N), c->S2, M)};
     // H'' = D Hs D^T and S'' = D S D^T are symmetric (Eq. 15): their upper block triangles are
-    // computed and mirrored (square products only: not with paired rows)
-    if (Mo == M) ops[2].tri = ops[3].tri = 1;
+    // computed (square products only: not with paired rows), which is all that is read of them
+    if (Mo == M) ops[2].tri = ops[3].tri = 2;
     paired(c, ops, 4);
     TRY(gemm(c, d, ops, 4, done));
   }
   TRY(prof_mark(c));
-  HIPCHK(c, line_search(c->HW, c->SW, c->H1, c->S1, c->H2, c->S2, M, c->partials, c->st,
-                        c->stream));
-  TRY(prof_mark(c));
-  if (fuse) {  // with the planes of the new HC, SC and of their transposes
-    const StatePlanes sp{c->HC_p.hi,  c->HC_p.lo,  c->SC_p.hi,  c->SC_p.lo,
-                         c->HCt_p.hi, c->HCt_p.lo, c->SCt_p.hi, c->SCt_p.lo,
-                         c->HC_p.ld,  c->HCt_p.ld};
-    if (hdf)
-      HIPCHK(c, (update_coefficients_split<T, float>(w.C, c->D_p.hi, c->D_p.ld, w.HC, w.HDf, w.SC,
-                                                    w.SDf, M, N, sp, c->st, c->stream)));
-    else
-      HIPCHK(c, update_coefficients_split<T>(w.C, c->D_p.hi, c->D_p.ld, w.HC, w.HD, w.SC,
-                                             sid ? nullptr : w.SD, M, N, sp, c->st, c->stream));
-  } else {
-    if (hdf)
-      HIPCHK(c, (update_coefficients<T, float>(w.C, w.D, w.HC, w.HDf, w.SC, w.SDf, mn, c->st,
-                                              c->stream)));
-    else
-      HIPCHK(c, update_coefficients<T>(w.C, w.D, w.HC, w.HD, w.SC, SD, mn, c->st, c->stream));
-    if (bf) TRY(split_state(c, w.HC, w.SC));
+  // with the planes of the new HW, SW (the gradient's operand) and of HC, SC and their transposes
+  Subspace mm{c->HW, c->SW, c->H1, c->S1, c->H2, c->S2, M, nullptr, nullptr, nullptr, nullptr, 0};
+  if (fuse) {
+    mm.hw_hi = c->HW_p.hi; mm.hw_lo = c->HW_p.lo;
+    mm.sw_hi = c->SW_p.hi; mm.sw_lo = c->SW_p.lo;
+    mm.ldp = c->HW_p.ld;
   }
-  HIPCHK(c, update_subspace(c->HW, c->SW, c->H1, c->S1, c->H2, c->S2, M, c->partials, c->st,
-                            trace, c->stream));
+  double* lpart = c->partials;
+  double* epart = c->partials + (size_t)RED_BLOCKS * NCOEF;
+  const bool fline = line_fused(M);
+  HIPCHK(c, line_search(mm, lpart, c->st, fline, c->stream));
+  TRY(prof_mark(c));
+  const StatePlanes sp{c->HC_p.hi,  c->HC_p.lo,  c->SC_p.hi,  c->SC_p.lo,
+                       c->HCt_p.hi, c->HCt_p.lo, c->SCt_p.hi, c->SCt_p.lo,
+                       c->HC_p.ld,  c->HCt_p.ld};
+  auto update = [&](auto* HD, auto* SDx) -> hipError_t {  // HD, SD in the products' type
+    typedef typename std::remove_pointer<decltype(HD)>::type TD;
+    if (fuse && fline)
+      return update_split_line<T, TD>(w.C, c->D_p.hi, c->D_p.ld, w.HC, HD, w.SC, sid ? nullptr : SDx, M, N, sp,
+                                      mm, lpart, epart, c->st, trace, c->stream);
+    if (fuse)
+      return update_coefficients_split<T, TD>(w.C, c->D_p.hi, c->D_p.ld, w.HC, HD, w.SC, sid ? nullptr : SDx,
+                                              M, N, sp, c->st, c->stream);
+    if (fline)
+      return update_line<T, TD>(w.C, w.D, w.HC, HD, w.SC, SDx, mn, mm, lpart, epart, c->st, trace, c->stream);
+    return update_coefficients<T, TD>(w.C, w.D, w.HC, HD, w.SC, SDx, mn, c->st, c->stream);
+  };
+  if (hdf) HIPCHK(c, update(w.HDf, w.SDf));
+  else HIPCHK(c, update(w.HD, SD));
+  if (!fline) HIPCHK(c, update_subspace(mm, epart, c->st, trace, c->stream));
+  if (bf && !fuse) {
+    TRY(split_state(c, w.HC, w.SC));
+    TRY(split_subspace(c));
+  }
   TRY(prof_mark(c));
   return OMM_OK;
 }
@@ -1157,6 +1172,7 @@ int resync_fp64(omm_ctx* c) {
   TRY(gemm(c, d, ops2, 2, nullptr));
   // the BF16x3 products read HC and SC through their planes
   TRY(split_state(c, w.HC, w.SC, false));
+  TRY(split_subspace(c, false));
   const int it = c->st_host->iter;
   TRY(ensure_trace(c, c->trace_off + it + 2));
   HIPCHK(c, energy_init(c->HW, c->SW, M, c->partials, c->st, c->trace + c->trace_off + it,
@@ -1271,6 +1287,7 @@ int minimize_impl(omm_ctx* c, const double* C0, bool C0_device, double eta, doub
     TRY(phase_begin<double>(c, c->w64, CF64, c->Hs, c->S, tol, 0));
     TRY(alloc_iter_planes(c));
     TRY(split_state(c, c->w64.HC, c->w64.SC, false));
+    TRY(split_subspace(c, false));
     c->phase_prec = OMM_BF16X3;
     c->phase_mixed64 = true;
     c->since_resync = 0;

@@ -43,7 +43,7 @@ template <typename TC>
 __global__ __launch_bounds__(256) void mirror_lower(GemmBatch batch, const int* done) {
   if (done && *done) return;
   const GemmOp& op = batch.op[blockIdx.z];
-  if (!op.tri) return;
+  if (op.tri != 1) return;
   const int bi = blockIdx.y * 32, bj = blockIdx.x * 32;  // destination block (rows bi, cols bj)
   if (bj > bi || bi >= op.M) return;
   __shared__ TC t[32][33];
@@ -57,6 +57,28 @@ __global__ __launch_bounds__(256) void mirror_lower(GemmBatch batch, const int* 
   for (int r = ty; r < 32; r += 8) {
     const int i = bi + r, j = bj + tx;
     if (i < op.M && j < op.N && i > j) C[(int64_t)i * op.ldc + j] = t[tx][r];
+  }
+}
+// The second half of the rows of every paired product (see GemmOp) and of its planes, from the first: a
+// pass of its own for the staged and BF16 tiles (in their epilogue it costs the direct-to-LDS tile
+// registers: 292 -> 361 us for the block-sparse [HD | SD] of 6500 orbitals).
+template <typename TC>
+__global__ __launch_bounds__(256) void pair_fill(GemmBatch batch, const int* done) {
+  if (done && *done) return;
+  const GemmOp& op = batch.op[blockIdx.z];
+  if (!op.pair_rows) return;
+  const int half = op.N >> 1, c = blockIdx.x * 256 + threadIdx.x;
+  if (c >= op.N) return;
+  const bool neg = c < half;
+  const int src = neg ? c + half : c - half;
+  const unsigned short sgn = neg ? 0x8000 : 0;  // bf16 rounding is symmetric in the sign
+  TC* C = static_cast<TC*>(op.C);
+  unsigned short* planes[2] = {static_cast<unsigned short*>(op.Chi), static_cast<unsigned short*>(op.Clo)};
+  for (int r = blockIdx.y; r < op.M; r += gridDim.y) {
+    const TC v = C[(int64_t)r * op.ldc + src];
+    C[(int64_t)(r + op.pair_rows) * op.ldc + c] = neg ? -v : v;
+    for (unsigned short* p : planes)
+      if (p) p[(int64_t)(r + op.pair_rows) * op.ldp + c] = p[(int64_t)r * op.ldp + src] ^ sgn;
   }
 }
 }  // namespace
@@ -282,18 +304,26 @@ hipError_t gemm_launch(const GemmDesc& d, const GemmOp* ops, int nops, const int
   for (int i = 0; i < nops; ++i) {
     if (!ops[i].tri) continue;
     if (ops[i].M != ops[i].N || ops[i].Chi || ops[i].kptr) return hipErrorInvalidValue;
-    tri = true;
+    tri |= ops[i].tri == 1;
   }
   hipError_t e = launch_products(d, ops, nops, done, ws, ws_bytes, s);
-  // the small tiles write both halves of a symmetric result themselves
-  if (e != hipSuccess || !tri || ops[0].M <= 0 || tile_direct(d.tile)) return e;
+  // the small tiles write both halves of symmetric and paired results themselves
+  if (e != hipSuccess || ops[0].M <= 0 || tile_direct(d.tile)) return e;
   GemmBatch b;
-  for (int i = 0; i < nops; ++i) b.op[i] = ops[i];
-  const int nb = (ops[0].M + 31) / 32;
-  if (d.tc == T_F64)
-    hipLaunchKernelGGL(mirror_lower<double>, dim3(nb, nb, nops), dim3(256), 0, s, b, done);
-  else
-    hipLaunchKernelGGL(mirror_lower<float>, dim3(nb, nb, nops), dim3(256), 0, s, b, done);
+  bool pairs = false;
+  for (int i = 0; i < nops; ++i) {
+    b.op[i] = ops[i];
+    pairs |= ops[i].pair_rows != 0;
+  }
+  if (tri) {
+    const int nb = (ops[0].M + 31) / 32;
+    hipLaunchKernelGGL(d.tc == T_F64 ? mirror_lower<double> : mirror_lower<float>, dim3(nb, nb, nops),
+                       dim3(256), 0, s, b, done);
+  }
+  if (pairs) {
+    const dim3 grid((ops[0].N + 255) / 256, std::min(ops[0].M, 4096), nops);
+    hipLaunchKernelGGL(d.tc == T_F64 ? pair_fill<double> : pair_fill<float>, grid, dim3(256), 0, s, b, done);
+  }
   return hipGetLastError();
 }
 

@@ -343,8 +343,14 @@ __device__ __forceinline__ void direct_tile(const GemmOp& op, int tm, int tn) {
         double v = op.alpha * s;
         if (op.X) v += op.beta * (double)ldg<TX>(op.X, (int64_t)row * op.ldx + col);
         if (!op.tri || row <= col) store_out<TC>(op, row, col, v);
+        if (op.pair_rows) {  // the pair rotation's element (see GemmOp), in place of a separate pass
+          const int half = op.N >> 1;
+          const TC c = (TC)v;
+          static_cast<TC*>(op.C)[(int64_t)(row + op.pair_rows) * op.ldc +
+                                 (col < half ? col + half : col - half)] = col < half ? c : -c;
+        }
         // symmetric result: the mirror element too, in place of a separate mirror pass
-        if (op.tri && row < col) store_out<TC>(op, col, row, v);
+        if (op.tri == 1 && row < col) store_out<TC>(op, col, row, v);
       }
     }
   }

@@ -389,26 +389,18 @@ struct AccT<CF64> {
   typedef d4 type;
 };
 
-// Stores output element (row, col) and, if the op asks for them, its bf16 planes; for the first half
-// of the rows of a paired result also the element's place in the second half (see GemmOp).
+// Stores output element (row, col) and, if the op asks for them, its bf16 planes.
 template <typename TC>
 __device__ __forceinline__ void store_out(const GemmOp& op, int row, int col, double v) {
   const TC c = (TC)v;
   static_cast<TC*>(op.C)[(int64_t)row * op.ldc + col] = c;
-  const int half = op.N >> 1, prow = row + op.pair_rows, pcol = col < half ? col + half : col - half;
-  if (op.pair_rows) static_cast<TC*>(op.C)[(int64_t)prow * op.ldc + pcol] = col < half ? c : -c;
   if (op.Chi) {
     const double w = (double)c;
     const unsigned short h = bf16_rne((float)w);
-    const int64_t e = (int64_t)row * op.ldp + col, pe = (int64_t)prow * op.ldp + pcol;
-    const unsigned short sgn = col < half ? 0 : 0x8000;  // bf16 rounding is symmetric in the sign
+    const int64_t e = (int64_t)row * op.ldp + col;
     static_cast<unsigned short*>(op.Chi)[e] = h;
-    if (op.pair_rows) static_cast<unsigned short*>(op.Chi)[pe] = h ^ sgn;
-    if (op.Clo) {  // null: the next product reads the hi plane alone
-      const unsigned short l = bf16_rne((float)(w - (double)bf16_val(h)));
-      static_cast<unsigned short*>(op.Clo)[e] = l;
-      if (op.pair_rows) static_cast<unsigned short*>(op.Clo)[pe] = l ^ sgn;
-    }
+    if (op.Clo)  // null: the next product reads the hi plane alone
+      static_cast<unsigned short*>(op.Clo)[e] = bf16_rne((float)(w - (double)bf16_val(h)));
   }
 }
 

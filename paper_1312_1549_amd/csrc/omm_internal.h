@@ -15,7 +15,7 @@ struct DevState {
   double E_prev;     // functional before the last line search
   double x;          // last line-search step
   double beta;       // last Polak-Ribiere coefficient
-  double pg_g;       // <PG, G> of the current gradient (denominator of the next beta)
+  double pg_g[2];    // <PG, G> by parity of the line search (denominator of the next beta)
   double alpha[5];   // last quartic coefficients
   double rel_change; // |2 (E - E_prev)| / |E + E_prev|
   double tol;
@@ -67,8 +67,8 @@ struct GemmOp {
   void* Chi;
   void* Clo;
   int64_t ldp;
-  // Symmetric result (M == N, no planes): only the tiles on and above the diagonal are computed
-  // and the launcher then copies C[j][i] into C[i][j] for every i > j.
+  // Symmetric result (M == N, no planes): only the tiles on and above the diagonal are computed. 1:
+  // the launch also leaves C[j][i] in C[i][j] for every i > j; 2: the readers take the upper half alone.
   int tri;
   // KCUT_* bits: known zeros of a triangular operand, skipped by the small tiles (one segment; the
   // others multiply them).
@@ -162,18 +162,28 @@ hipError_t store_inputs(const SymInputs& in, int64_t n, hipStream_t s);
 hipError_t energy_init(const double* HW, const double* SW, int M, double* partials, DevState* st,
                        double* trace, hipStream_t s);
 
-// Polak-Ribiere beta and D = -PG + beta D. With `hi` non-null D is rounded to bf16 and its bits
+// Polak-Ribiere beta (0 in line search k = 0) and D = -PG + beta D. With `hi` non-null D is rounded to bf16 and its bits
 // are written to `hi` (the single-plane operand of the two-product GEMMs; rows of length ld,
 // n / cols of them); the previous direction is then read back from `hi`, and D, which may be
 // null, only receives a copy of the rounded values.
 template <typename T, typename TP = T, typename TG = T>
-hipError_t beta_and_direction(const TG* G, const TP* PG, const TG* Gprev, T* D, int64_t n, int first,
+hipError_t beta_and_direction(const TG* G, const TP* PG, const TG* Gprev, T* D, int64_t n, int k,
                               double* partials, DevState* st, hipStream_t s,
                               unsigned short* hi = nullptr, int64_t cols = 0, int64_t ld = 0);
 
-hipError_t line_search(const double* HW, const double* SW, const double* H1, const double* S1,
-                       const double* H2, const double* S2, int M, double* partials, DevState* st,
-                       hipStream_t s);
+// HW, SW (symmetric) and H', S', H'', S'' (only the upper halves of the last two are read), M x M, and
+// optional bf16 planes of HW, SW (row length ldp) that the update writes.
+struct Subspace {
+  double *HW, *SW;
+  const double *H1, *S1, *H2, *S2;
+  int M;
+  unsigned short *hw_hi, *hw_lo, *sw_hi, *sw_lo;
+  int64_t ldp;
+};
+// Partial sums of the quartic's terms into `partials`, then (unless fused) its line minimum. `fused`
+// (line_fused(M)): the update that follows (update_line, update_split_line) finds the minimum itself.
+bool line_fused(int M);
+hipError_t line_search(const Subspace& m, double* partials, DevState* st, bool fused, hipStream_t s);
 
 // HD, SD (type TD) may be held in a narrower type than the state (FP32 products of the BF16
 // scheme with an FP64 state).
@@ -197,9 +207,19 @@ hipError_t update_coefficients_split(T* C, const unsigned short* Dh, int64_t ldd
                                      const TD* HD, T* SC, const TD* SD, int rows, int cols,
                                      const StatePlanes& p, const DevState* st, hipStream_t s);
 
-hipError_t update_subspace(double* HW, double* SW, const double* H1, const double* S1,
-                           const double* H2, const double* S2, int M, double* partials,
-                           DevState* st, double* trace, hipStream_t s);
+hipError_t update_subspace(const Subspace& m, double* partials, DevState* st, double* trace, hipStream_t s);
+
+// The line minimum from `lpart`, update_coefficients (update_coefficients_split) and update_subspace in
+// one launch; `epart` is another partials array.
+template <typename T, typename TD = T>
+hipError_t update_line(T* C, const T* D, T* HC, const TD* HD, T* SC, const TD* SD, int64_t n,
+                       const Subspace& m, const double* lpart, double* epart, DevState* st,
+                       double* trace, hipStream_t s);
+template <typename T, typename TD = T>
+hipError_t update_split_line(T* C, const unsigned short* Dh, int64_t ldd, T* HC, const TD* HD, T* SC,
+                             const TD* SD, int rows, int cols, const StatePlanes& p, const Subspace& m,
+                             const double* lpart, double* epart, DevState* st, double* trace,
+                             hipStream_t s);
 
 hipError_t identity_minus(const double* SW, double* out, int M, double diag, double scale,
                           hipStream_t s);

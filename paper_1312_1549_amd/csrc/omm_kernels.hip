@@ -16,9 +16,29 @@ constexpr int NT = 256;
 // block-reduction scratch: up to NCOEF values at once (block_sums), one slot per wave each
 constexpr int SH_SUMS = NCOEF * (NT / 64);
 
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+// Sum over the wave (fixed order), in every lane: rotations within the rows of 16 lanes, then the four
+// row sums. Register moves only (a shuffle down goes through LDS twice per step).
+__device__ __forceinline__ double wave_sum(double v) {
+  v = dpp_add<0x121>(v);
+  v = dpp_add<0x122>(v);
+  v = dpp_add<0x124>(v);
+  v = dpp_add<0x128>(v);
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
 // Sum of `v` over the block (FP64, fixed order). Result valid in thread 0.
 __device__ __forceinline__ double block_sum(double v, double* sh) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+  v = wave_sum(v);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   __syncthreads();
   if (lane == 0) sh[w] = v;
@@ -34,9 +54,7 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
 template <int W>
 __device__ __forceinline__ void block_sums(double (&v)[W], double* sh) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-    for (int k = 0; k < W; ++k) v[k] += __shfl_down(v[k], o, 64);
+  for (int k = 0; k < W; ++k) v[k] = wave_sum(v[k]);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   __syncthreads();
   if (lane == 0)
@@ -401,30 +419,34 @@ __global__ void k_pr_partials4(const TG* G, const TP* PG, const TG* Gp, int64_t 
   }
 }
 
-__device__ __forceinline__ void f_pr_final(const double* partials, int nb, int first, DevState* st) {
-  if (st->done) return;
+// Polak-Ribiere beta from the partial sums, in every thread (each block sums them itself, in the same
+// order: a launch of its own for this took 4.5 us of every line search). One block (`writer`) keeps it
+// in the state, with <PG, G>, whose two slots alternate so that no block reads what another
+// writes.
+__device__ __forceinline__ double beta_of(const double* partials, int nb, int first, int parity,
+                                          DevState* st, bool writer) {
   __shared__ double sh[SH_SUMS];
-  double s2v[2];
-  sum_partials_all<2>(partials, nb, sh, s2v);
-  const double s1 = s2v[0], s2 = s2v[1];
-  if (threadIdx.x != 0) return;
-  double beta = 0.0;
-  if (!first) {
-    beta = (s1 - s2) / st->pg_g;
-    if (!isfinite(beta)) beta = 0.0;
+  __shared__ double shared_beta;
+  double v[2];
+  sum_partials_all<2>(partials, nb, sh, v);
+  if (threadIdx.x == 0) {
+    double beta = 0.0;
+    if (!first) {
+      beta = (v[0] - v[1]) / st->pg_g[parity ^ 1];
+      if (!isfinite(beta)) beta = 0.0;
+    }
+    shared_beta = beta;
+    if (writer) {
+      st->beta = beta;
+      st->pg_g[parity] = v[0];
+    }
   }
-  st->beta = beta;
-  st->pg_g = s1;
-}
-
-__global__ void k_pr_final(const double* partials, int nb, int first, DevState* st) {
-  f_pr_final(partials, nb, first, st);
+  __syncthreads();
+  return shared_beta;
 }
 
 template <typename T, typename TP = T>
-__device__ __forceinline__ void b_direction(const TP* PG, T* D, int64_t n, int first, const DevState* st, int bid, int nb) {
-  if (st->done) return;
-  const double beta = st->beta;
+__device__ __forceinline__ void b_direction(const TP* PG, T* D, int64_t n, int first, double beta, int bid, int nb) {
   for (int64_t i = (int64_t)bid * NT + threadIdx.x; i < n; i += (int64_t)nb * NT) {
     const double d = first ? -(double)PG[i] : -(double)PG[i] + beta * (double)D[i];
     D[i] = (T)d;
@@ -447,18 +469,22 @@ __global__ void k_block_pattern(const double* B, int64_t n, unsigned char* flags
 }
 
 template <typename T, typename TP>
-__global__ void k_direction(const TP* PG, T* D, int64_t n, int first, const DevState* st) {
-  b_direction(PG, D, n, first, st, blockIdx.x, gridDim.x);
+__global__ __launch_bounds__(NT) void k_direction(const TP* PG, T* D, int64_t n, int first, int parity,
+                                                 const double* partials, int np, DevState* st) {
+  if (st->done) return;
+  const double beta = beta_of(partials, np, first, parity, st, blockIdx.x == 0);
+  b_direction(PG, D, n, first, beta, blockIdx.x, gridDim.x);
 }
 
 // The same direction rounded to bf16: D keeps the rounded values (exact in T) and `hi` their bf16
 // bits (rows of length ld), so the products with D need no lo plane and the CG update moves along
 // exactly this D. One row of D (rows x cols) per blockIdx.y.
 template <typename T, typename TP>
-__global__ void k_direction_bf16(const TP* PG, T* D, unsigned short* hi, int64_t rows, int64_t cols,
-                                 int64_t ld, int first, const DevState* st) {
+__global__ __launch_bounds__(NT) void k_direction_bf16(const TP* PG, T* D, unsigned short* hi, int64_t rows,
+                                                      int64_t cols, int64_t ld, int first, int parity,
+                                                      const double* partials, int np, DevState* st) {
   if (st->done) return;
-  const double beta = st->beta;
+  const double beta = beta_of(partials, np, first, parity, st, blockIdx.x == 0 && blockIdx.y == 0);
   for (int64_t r = blockIdx.y; r < rows; r += gridDim.y)
     for (int64_t c = (int64_t)blockIdx.x * NT + threadIdx.x; c < cols;
          c += (int64_t)gridDim.x * NT) {
@@ -476,13 +502,15 @@ __global__ void k_direction_bf16(const TP* PG, T* D, unsigned short* hi, int64_t
 // The same, four columns per thread (cols and ld multiples of 4, aligned rows) and four rows per
 // block, all loads of a block's rows issued before its stores.
 template <typename T, typename TP>
-__global__ void k_direction_bf16x4(const TP* PG, T* D, unsigned short* hi, int64_t rows,
-                                   int64_t cols, int64_t ld, int first, const DevState* st) {
+__global__ __launch_bounds__(NT) void k_direction_bf16x4(const TP* PG, T* D, unsigned short* hi,
+                                                        int64_t rows, int64_t cols, int64_t ld,
+                                                        int first, int parity, const double* partials,
+                                                        int np, DevState* st) {
   if (st->done) return;
   typedef TP P4 __attribute__((ext_vector_type(4)));
   typedef unsigned short U4 __attribute__((ext_vector_type(4)));
   constexpr int RB = 4;
-  const double beta = st->beta;
+  const double beta = beta_of(partials, np, first, parity, st, blockIdx.x == 0 && blockIdx.y == 0);
   const int64_t c = (int64_t)blockIdx.x * NT + threadIdx.x;
   if (4 * c >= cols) return;
   for (int64_t r0 = (int64_t)blockIdx.y * RB; r0 < rows; r0 += (int64_t)gridDim.y * RB) {
@@ -568,10 +596,68 @@ __device__ __forceinline__ void b_coef_partials(const double* HW, const double* 
     for (int k = 0; k < NCOEF; ++k) partials[bid * NCOEF + k] = acc[k];
 }
 
-__global__ void k_coef_partials(const double* HW, const double* SW, const double* H1,
-                                const double* S1, const double* H2, const double* S2, int M,
-                                double* partials, const DevState* st) {
-  b_coef_partials(HW, SW, H1, S1, H2, S2, M, partials, st, blockIdx.x, gridDim.x);
+// Pair p of the tile pairs (bi <= bj) of a T x T tiling.
+__device__ __forceinline__ void tile_pair(int p, int T, int& bi, int& bj) {
+  bi = 0;
+  while (p >= T - bi) {
+    p -= T - bi;
+    ++bi;
+  }
+  bj = bi + p;
+}
+
+// The same sums for one system over pairs of 32 x 32 tiles: HW, SW, H'' and S'' are symmetric and only
+// their upper halves are read, H' and S' wholly, the mirror tile through LDS.
+__global__ __launch_bounds__(NT) void k_coef_sym(Subspace m, double* partials, const DevState* st) {
+  if (st->done) return;
+  __shared__ double th[32][33], ts[32][33];
+  __shared__ double sh[SH_SUMS];
+  double acc[NCOEF];
+#pragma unroll
+  for (int k = 0; k < NCOEF; ++k) acc[k] = 0.0;
+  const int M = m.M, T = (M + 31) / 32, npairs = T * (T + 1) / 2;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int p = blockIdx.x; p < npairs; p += gridDim.x) {
+    int bi, bj;
+    tile_pair(p, T, bi, bj);
+    const int i0 = bi * 32, j0 = bj * 32;
+    __syncthreads();
+    for (int r = ty; r < 32; r += 8) {
+      const int i = j0 + r, j = i0 + tx;
+      const bool in = i < M && j < M;
+      th[r][tx] = in ? m.H1[(int64_t)i * M + j] : 0.0;
+      ts[r][tx] = in ? m.S1[(int64_t)i * M + j] : 0.0;
+    }
+    __syncthreads();
+    for (int r = ty; r < 32; r += 8) {
+      const int i = i0 + r, j = j0 + tx;
+      if (i >= M || j >= M || i > j) continue;
+      const int64_t e = (int64_t)i * M + j;
+      const double hw = m.HW[e], sw = m.SW[e], h2 = m.H2[e], s2 = m.S2[e];
+      const double h1 = m.H1[e], s1 = m.S1[e];
+      if (i == j) {
+        acc[0] += hw; acc[1] += h1; acc[2] += h2;
+        acc[3] += sw * hw; acc[4] += s1 * hw; acc[5] += sw * h1; acc[6] += s2 * hw; acc[7] += sw * h2;
+        acc[8] += s1 * h1; acc[9] += s1 * h1; acc[10] += s2 * h1; acc[11] += s1 * h2; acc[12] += s2 * h2;
+      } else {
+        const double h1t = th[tx][r], s1t = ts[tx][r];  // H'_ji, S'_ji
+        const double h1s = h1 + h1t, s1s = s1 + s1t;
+        acc[3] += 2.0 * sw * hw;
+        acc[4] += s1s * hw;
+        acc[5] += sw * h1s;
+        acc[6] += 2.0 * s2 * hw;
+        acc[7] += 2.0 * sw * h2;
+        acc[8] += s1 * h1t + s1t * h1;
+        acc[9] += s1 * h1 + s1t * h1t;
+        acc[10] += s2 * h1s;
+        acc[11] += s1s * h2;
+        acc[12] += 2.0 * s2 * h2;
+      }
+    }
+  }
+  block_sums<NCOEF>(acc, sh);
+  if (threadIdx.x == 0)
+    for (int k = 0; k < NCOEF; ++k) partials[blockIdx.x * NCOEF + k] = acc[k];
 }
 
 // Line minimum of q(x) = sum_k a_k x^k: the first local minimum met going downhill from x = 0
@@ -651,36 +737,58 @@ __device__ int line_minimum(const double* a, double* xout) {
   return found;
 }
 
-__device__ __forceinline__ void f_line_final(const double* partials, int nb, DevState* st) {
-  if (st->done) return;
-  __shared__ double sh[SH_SUMS];
-  double s[NCOEF];
-  sum_partials_all<NCOEF>(partials, nb, sh, s);
-  if (threadIdx.x != 0) return;
-  double a[5];
-  a[0] = 4.0 * s[0] - 2.0 * s[3];
-  a[1] = 8.0 * s[1] - 4.0 * s[4] - 4.0 * s[5];
-  a[2] = 4.0 * s[2] - 2.0 * s[6] - 2.0 * s[7] - 4.0 * s[8] - 4.0 * s[9];
-  a[3] = -4.0 * s[10] - 4.0 * s[11];
-  a[4] = -2.0 * s[12];
-  for (int k = 0; k < 5; ++k) st->alpha[k] = a[k];
-  for (int k = 0; k < 5; ++k)
-    if (!isfinite(a[k])) { st->done = -5; return; }
-  double x = 0.0;
-  if (!line_minimum(a, &x)) { st->done = -7; return; }
-  st->x = x;
+// The quartic of the line search from the partial sums of its 13 terms and its minimum x, in every thread
+// of the block (false: none). Wave w sums columns w, w + 4, ..; the same sums in every block that
+// calls this, so that a kernel may find x for itself; one block (`writer`) keeps the result, or the
+// error, in the state.
+__device__ __forceinline__ bool line_x(const double* partials, int nb, DevState* st, bool writer,
+                                       double* xout) {
+  __shared__ double s[NCOEF];
+  __shared__ double xs;
+  __shared__ int found;
+  const int lane = threadIdx.x & 63;
+  for (int c = threadIdx.x >> 6; c < NCOEF; c += NT / 64) {
+    double v = 0.0;
+    for (int r = lane; r < nb; r += 64) v += partials[r * NCOEF + c];
+    v = wave_sum(v);
+    if (lane == 0) s[c] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double a[5];
+    a[0] = 4.0 * s[0] - 2.0 * s[3];
+    a[1] = 8.0 * s[1] - 4.0 * s[4] - 4.0 * s[5];
+    a[2] = 4.0 * s[2] - 2.0 * s[6] - 2.0 * s[7] - 4.0 * s[8] - 4.0 * s[9];
+    a[3] = -4.0 * s[10] - 4.0 * s[11];
+    a[4] = -2.0 * s[12];
+    int code = 0;
+    for (int k = 0; k < 5; ++k)
+      if (!isfinite(a[k])) code = -5;
+    double x = 0.0;
+    if (code == 0 && !line_minimum(a, &x)) code = -7;
+    if (writer) {
+      for (int k = 0; k < 5; ++k) st->alpha[k] = a[k];
+      if (code) st->done = code;
+      else st->x = x;
+    }
+    xs = x;
+    found = code == 0;
+  }
+  __syncthreads();
+  *xout = xs;
+  return found != 0;
 }
 
-__global__ void k_line_final(const double* partials, int nb, DevState* st) {
-  f_line_final(partials, nb, st);
+__global__ __launch_bounds__(NT) void k_line_final(const double* partials, int nb, DevState* st) {
+  if (st->done) return;
+  double x;
+  line_x(partials, nb, st, true, &x);
 }
 
 // ---- updates (Eq. 16 and the footnote of Sec. 2.3) ----------------------------------------------
 template <typename T, typename TD = T>
 __device__ __forceinline__ void b_update_mn(T* C, const T* D, T* HC, const TD* HD, T* SC, const TD* SD, int64_t n,
-                            const DevState* st, int bid, int nb) {
-  if (st->done) return;
-  const double x = st->x;
+                            double x, int bid, int nb) {
   for (int64_t i = (int64_t)bid * NT + threadIdx.x; i < n; i += (int64_t)nb * NT) {
     C[i] = (T)((double)C[i] + x * (double)D[i]);
     HC[i] = (T)((double)HC[i] + x * (double)HD[i]);
@@ -691,7 +799,8 @@ __device__ __forceinline__ void b_update_mn(T* C, const T* D, T* HC, const TD* H
 template <typename T, typename TD>
 __global__ void k_update_mn(T* C, const T* D, T* HC, const TD* HD, T* SC, const TD* SD, int64_t n,
                             const DevState* st) {
-  b_update_mn(C, D, HC, HD, SC, SD, n, st, blockIdx.x, gridDim.x);
+  if (st->done) return;
+  b_update_mn(C, D, HC, HD, SC, SD, n, st->x, blockIdx.x, gridDim.x);
 }
 
 __device__ __forceinline__ void split_store(double v, unsigned short* hi, unsigned short* lo,
@@ -762,17 +871,16 @@ __device__ __forceinline__ void stream_store(unsigned w, unsigned short* dst) {
   __builtin_nontemporal_store(w, reinterpret_cast<unsigned*>(dst));
 }
 
+typedef unsigned PlaneTile[64][65];
+
 template <typename T, typename TD>
-__global__ __launch_bounds__(NT) void k_update_split_mn2(T* C, const unsigned short* Dh,
-                                                         int64_t ldd, T* HC, const TD* HD, T* SC,
-                                                         const TD* SD, int rows, int cols,
-                                                         StatePlanes p, const DevState* st) {
-  if (st->done) return;
+__device__ __forceinline__ void b_update_split_mn2(T* C, const unsigned short* Dh, int64_t ldd, T* HC,
+                                                   const TD* HD, T* SC, const TD* SD, int rows, int cols,
+                                                   const StatePlanes& p, double x, int bx, int by,
+                                                   PlaneTile& th, PlaneTile& ts) {
   typedef T T2 __attribute__((ext_vector_type(2)));
   typedef TD TD2 __attribute__((ext_vector_type(2)));
-  __shared__ unsigned th[64][65], ts[64][65];
-  const double x = st->x;
-  const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
+  const int c0 = bx * 64, r0 = by * 64;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 column pairs x 8 rows
   const int gc = c0 + 2 * tx;
   // rows ty + 8 k, four at a time: all loads of a batch are issued before its stores
@@ -854,6 +962,16 @@ __global__ __launch_bounds__(NT) void k_update_split_mn2(T* C, const unsigned sh
   }
 }
 
+template <typename T, typename TD>
+__global__ __launch_bounds__(NT) void k_update_split_mn2(T* C, const unsigned short* Dh,
+                                                         int64_t ldd, T* HC, const TD* HD, T* SC,
+                                                         const TD* SD, int rows, int cols,
+                                                         StatePlanes p, const DevState* st) {
+  if (st->done) return;
+  __shared__ PlaneTile th, ts;
+  b_update_split_mn2(C, Dh, ldd, HC, HD, SC, SD, rows, cols, p, st->x, blockIdx.x, blockIdx.y, th, ts);
+}
+
 // HW += x (H' + H'^T) + x^2 H'', SW likewise; partial sums of Tr HW, <SW, HW>, Tr SW.
 __device__ __forceinline__ void b_update_mm(double* HW, double* SW, const double* H1, const double* S1,
                             const double* H2, const double* S2, int M, double* partials,
@@ -902,27 +1020,32 @@ __device__ __forceinline__ void b_update_mm(double* HW, double* SW, const double
 // The same update for one system, using that HW, SW, H'' and S'' are symmetric: each block takes a
 // pair of 32 x 32 tiles (bi, bj), bi <= bj, computes the upper one from the upper tiles of HW,
 // SW, H'', S'' and both tiles of H', S' (the mirror one transposed through LDS), and writes the
-// result to both (on a diagonal tile, its upper triangle to both halves). HW and SW come out
-// exactly symmetric; every element of H', S' and of the upper halves is read once.
-__global__ __launch_bounds__(NT) void k_update_mm_sym(double* HW, double* SW, const double* H1,
-                                                      const double* S1, const double* H2,
-                                                      const double* S2, int M, double* partials,
-                                                      const DevState* st) {
-  if (st->done) return;
-  __shared__ double th[32][33], ts[32][33], oh[32][33], os[32][33];
+// result to both (on a diagonal tile, its upper triangle to both halves), with its bf16 planes if
+// there are any. HW and SW come out exactly symmetric; every element of H', S' and of the upper halves
+// is read once.
+typedef double MMTile[32][33];
+
+__device__ __forceinline__ void mm_store(const Subspace& m, int i, int j, double hw, double sw) {
+  const int64_t e = (int64_t)i * m.M + j;
+  m.HW[e] = hw;
+  m.SW[e] = sw;
+  if (m.hw_hi) {
+    const int64_t q = (int64_t)i * m.ldp + j;
+    split_store(hw, m.hw_hi, m.hw_lo, q);
+    split_store(sw, m.sw_hi, m.sw_lo, q);
+  }
+}
+
+__device__ __forceinline__ void b_update_mm_sym(const Subspace& m, double x, double* partials, int bid, int nb,
+                                                MMTile (&t)[4]) {
   __shared__ double sh[SH_SUMS];
-  const double x = st->x;
+  MMTile &th = t[0], &ts = t[1], &oh = t[2], &os = t[3];
   double tr = 0.0, f = 0.0, trs = 0.0;
-  const int T = (M + 31) / 32;
-  const int npairs = T * (T + 1) / 2;
+  const int M = m.M, T = (M + 31) / 32, npairs = T * (T + 1) / 2;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int p = blockIdx.x; p < npairs; p += gridDim.x) {
-    int bi = 0, rem = p;
-    while (rem >= T - bi) {
-      rem -= T - bi;
-      ++bi;
-    }
-    const int bj = bi + rem;
+  for (int p = bid; p < npairs; p += nb) {
+    int bi, bj;
+    tile_pair(p, T, bi, bj);
     const int i0 = bi * 32, j0 = bj * 32;
     const bool diag = bi == bj;
     __syncthreads();
@@ -930,18 +1053,17 @@ __global__ __launch_bounds__(NT) void k_update_mm_sym(double* HW, double* SW, co
     for (int rr = ty; rr < 32; rr += 8) {
       const int i = j0 + rr, j = i0 + tx;
       const bool in = i < M && j < M;
-      th[rr][tx] = in ? H1[(int64_t)i * M + j] : 0.0;
-      ts[rr][tx] = in ? S1[(int64_t)i * M + j] : 0.0;
+      th[rr][tx] = in ? m.H1[(int64_t)i * M + j] : 0.0;
+      ts[rr][tx] = in ? m.S1[(int64_t)i * M + j] : 0.0;
     }
     __syncthreads();
     for (int r = ty; r < 32; r += 8) {
       const int i = i0 + r, j = j0 + tx;
       if (i < M && j < M && (!diag || r <= tx)) {
         const int64_t e = (int64_t)i * M + j;
-        const double hw = HW[e] + x * H1[e] + x * th[tx][r] + x * x * H2[e];
-        const double sw = SW[e] + x * S1[e] + x * ts[tx][r] + x * x * S2[e];
-        HW[e] = hw;
-        SW[e] = sw;
+        const double hw = m.HW[e] + x * m.H1[e] + x * th[tx][r] + x * x * m.H2[e];
+        const double sw = m.SW[e] + x * m.S1[e] + x * ts[tx][r] + x * x * m.S2[e];
+        mm_store(m, i, j, hw, sw);
         oh[r][tx] = hw;
         os[r][tx] = sw;
         if (diag && r == tx) {
@@ -957,21 +1079,55 @@ __global__ __launch_bounds__(NT) void k_update_mm_sym(double* HW, double* SW, co
     // mirror: element (j0 + rr, i0 + tx) = output (i0 + tx, j0 + rr)
     for (int rr = ty; rr < 32; rr += 8) {
       const int i = j0 + rr, j = i0 + tx;
-      if (i < M && j < M && (!diag || tx < rr)) {
-        const int64_t e = (int64_t)i * M + j;
-        HW[e] = oh[tx][rr];
-        SW[e] = os[tx][rr];
-      }
+      if (i < M && j < M && (!diag || tx < rr)) mm_store(m, i, j, oh[tx][rr], os[tx][rr]);
     }
   }
   double v3[3] = {tr, f, trs};
   block_sums<3>(v3, sh);
-  const double a = v3[0], b = v3[1], c = v3[2];
-  if (threadIdx.x == 0) {
-    partials[blockIdx.x * 3 + 0] = a;
-    partials[blockIdx.x * 3 + 1] = b;
-    partials[blockIdx.x * 3 + 2] = c;
-  }
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) partials[bid * 3 + k] = v3[k];
+}
+
+__global__ __launch_bounds__(NT) void k_update_mm_sym(Subspace m, double* partials, const DevState* st) {
+  if (st->done) return;
+  __shared__ MMTile t[4];
+  b_update_mm_sym(m, st->x, partials, blockIdx.x, gridDim.x, t);
+}
+
+// Small systems: the line minimum and both updates in one launch. Every block finds x itself; the
+// first nmm then update HW and SW, the others C, HC, SC. `lpart` (np rows of the quartic's terms)
+// and `epart` (the energy's) are different arrays, since some blocks still read one while others
+// write the other.
+template <typename T, typename TD>
+__global__ __launch_bounds__(NT) void k_update_line(T* C, const T* D, T* HC, const TD* HD, T* SC, const TD* SD,
+                                                    int64_t n, Subspace m, int nmm, const double* lpart,
+                                                    int np, double* epart, DevState* st) {
+  if (st->done) return;
+  __shared__ MMTile t[4];
+  double x;
+  if (!line_x(lpart, np, st, blockIdx.x == 0, &x)) return;
+  const int bid = blockIdx.x;
+  if (bid < nmm) b_update_mm_sym(m, x, epart, bid, nmm, t);
+  else b_update_mn(C, D, HC, HD, SC, SD, n, x, bid - nmm, gridDim.x - nmm);
+}
+
+template <typename T, typename TD>
+__global__ __launch_bounds__(NT) void k_update_split_line(T* C, const unsigned short* Dh, int64_t ldd, T* HC,
+                                                          const TD* HD, T* SC, const TD* SD, int rows,
+                                                          int cols, StatePlanes p, Subspace m, int nmm,
+                                                          const double* lpart, int np, double* epart,
+                                                          DevState* st) {
+  if (st->done) return;
+  __shared__ union {
+    MMTile t[4];
+    PlaneTile u[2];
+  } lds;
+  double x;
+  if (!line_x(lpart, np, st, blockIdx.x == 0, &x)) return;
+  const int bid = blockIdx.x, tile = bid - nmm, bx = (cols + 63) / 64;
+  if (bid < nmm) b_update_mm_sym(m, x, epart, bid, nmm, lds.t);
+  else b_update_split_mn2(C, Dh, ldd, HC, HD, SC, SD, rows, cols, p, x, tile % bx, tile / bx, lds.u[0], lds.u[1]);
 }
 
 __device__ __forceinline__ void f_update_final(const double* partials, int nb, int M, DevState* st,
@@ -1036,19 +1192,16 @@ __global__ void g_pr_partials(const SysDev* sys, int parity, int first) {
   if (d.f64) g_pr_partials_t<double>(d, parity, first);
   else g_pr_partials_t<float>(d, parity, first);
 }
-__global__ void g_pr_final(const SysDev* sys, int first) {
-  const SysDev& d = sys[blockIdx.y];
-  f_pr_final(d.partials, GROUP_BLOCKS, first, d.st);
-}
 template <typename T>
 __device__ __forceinline__ void g_direction_t(const SysDev& d, int parity, int first) {
   const T* G = static_cast<const T*>(parity ? d.G1 : d.G0);
   const T* PG = d.precon ? static_cast<const T*>(d.PG) : G;
-  b_direction<T>(PG, static_cast<T*>(d.D), (int64_t)d.M * d.N, first, d.st, blockIdx.x,
-                 gridDim.x);
+  const double beta = beta_of(d.partials, GROUP_BLOCKS, first, parity, d.st, blockIdx.x == 0);
+  b_direction<T>(PG, static_cast<T*>(d.D), (int64_t)d.M * d.N, first, beta, blockIdx.x, gridDim.x);
 }
 __global__ void g_direction(const SysDev* sys, int parity, int first) {
   const SysDev& d = sys[blockIdx.y];
+  if (d.st->done) return;
   if (d.f64) g_direction_t<double>(d, parity, first);
   else g_direction_t<float>(d, parity, first);
 }
@@ -1058,16 +1211,19 @@ __global__ void g_coef_partials(const SysDev* sys) {
 }
 __global__ void g_line_final(const SysDev* sys) {
   const SysDev& d = sys[blockIdx.y];
-  f_line_final(d.partials, GROUP_BLOCKS, d.st);
+  if (d.st->done) return;
+  double x;
+  line_x(d.partials, GROUP_BLOCKS, d.st, true, &x);
 }
 template <typename T>
 __device__ __forceinline__ void g_update_mn_t(const SysDev& d) {
   b_update_mn<T>(static_cast<T*>(d.C), static_cast<const T*>(d.D), static_cast<T*>(d.HC),
                  static_cast<const T*>(d.HD), static_cast<T*>(d.SC), static_cast<const T*>(d.SD),
-                 (int64_t)d.M * d.N, d.st, blockIdx.x, gridDim.x);
+                 (int64_t)d.M * d.N, d.st->x, blockIdx.x, gridDim.x);
 }
 __global__ void g_update_mn(const SysDev* sys) {
   const SysDev& d = sys[blockIdx.y];
+  if (d.st->done) return;
   if (d.f64) g_update_mn_t<double>(d);
   else g_update_mn_t<float>(d);
 }
@@ -1080,10 +1236,9 @@ __global__ void g_update_final(const SysDev* sys) {
   f_update_final(d.partials, GROUP_BLOCKS, d.M, d.st, d.trace);
 }
 
-int tile_blocks(int M) {
-  const int tb = (M + 31) / 32;
-  int b = tb * tb;
-  return b > RED_BLOCKS ? RED_BLOCKS : b;
+int pair_blocks(int M) {
+  const int T = (M + 31) / 32, n = T * (T + 1) / 2;
+  return n < RED_BLOCKS ? n : RED_BLOCKS;
 }
 
 }  // namespace
@@ -1212,11 +1367,14 @@ hipError_t block_pattern(const double* B, int64_t n, unsigned char* flags, hipSt
 }
 
 template <typename T, typename TP, typename TG>
-hipError_t beta_and_direction(const TG* G, const TP* PG, const TG* Gprev, T* D, int64_t n, int first,
+hipError_t beta_and_direction(const TG* G, const TP* PG, const TG* Gprev, T* D, int64_t n, int k,
                               double* partials, DevState* st, hipStream_t s, unsigned short* hi,
                               int64_t cols, int64_t ld) {
   if (!hi && !D) return hipErrorInvalidValue;
+  const int first = k == 0 ? 1 : 0, parity = k & 1;
   const int nb = red_blocks(n);
+  // each direction block first sums the partials: no more blocks than run at once
+  constexpr int64_t DIR_BLOCKS = 2048;
   const bool vec = ((uintptr_t)G | (uintptr_t)Gprev) % (4 * sizeof(TG)) == 0 &&
                    (uintptr_t)PG % (4 * sizeof(TP)) == 0;
   if (vec)
@@ -1225,23 +1383,24 @@ hipError_t beta_and_direction(const TG* G, const TP* PG, const TG* Gprev, T* D, 
   else
     hipLaunchKernelGGL((k_pr_partials<TG, TP>), dim3(nb), dim3(NT), 0, s, G, PG, Gprev, n, first,
                        partials, st);
-  hipLaunchKernelGGL(k_pr_final, dim3(1), dim3(NT), 0, s, partials, nb, first, st);
   if (hi) {
     if (cols <= 0 || n % cols != 0 || ld < cols) return hipErrorInvalidValue;
     const int64_t rows = n / cols;
     const bool vec4 = cols % 4 == 0 && ld % 4 == 0 && (uintptr_t)PG % (4 * sizeof(TP)) == 0 &&
                       (uintptr_t)hi % 8 == 0;
-    if (vec4) {
-      const int64_t bx = (cols / 4 + NT - 1) / NT, by = (rows + 3) / 4;
-      hipLaunchKernelGGL((k_direction_bf16x4<T, TP>), dim3((unsigned)bx, (unsigned)(by < 65535 ? by : 65535)),
-                         dim3(NT), 0, s, PG, D, hi, rows, cols, ld, first, st);
-    } else {
-      const int64_t bx = (cols + NT - 1) / NT;
-      hipLaunchKernelGGL((k_direction_bf16<T, TP>), dim3((unsigned)bx, (unsigned)(rows < 65535 ? rows : 65535)),
-                         dim3(NT), 0, s, PG, D, hi, rows, cols, ld, first, st);
-    }
+    const int64_t bx = (cols / (vec4 ? 4 : 1) + NT - 1) / NT;
+    const int64_t by = std::min<int64_t>(vec4 ? (rows + 3) / 4 : rows,
+                                         std::max<int64_t>(1, DIR_BLOCKS / bx));
+    const dim3 grid((unsigned)bx, (unsigned)by);
+    if (vec4)
+      hipLaunchKernelGGL((k_direction_bf16x4<T, TP>), grid, dim3(NT), 0, s, PG, D, hi, rows, cols, ld,
+                         first, parity, partials, nb, st);
+    else
+      hipLaunchKernelGGL((k_direction_bf16<T, TP>), grid, dim3(NT), 0, s, PG, D, hi, rows, cols, ld, first,
+                         parity, partials, nb, st);
   } else {
-    hipLaunchKernelGGL((k_direction<T, TP>), dim3(ew_blocks(n)), dim3(NT), 0, s, PG, D, n, first, st);
+    hipLaunchKernelGGL((k_direction<T, TP>), dim3(std::min<int64_t>(ew_blocks(n), DIR_BLOCKS)), dim3(NT),
+                       0, s, PG, D, n, first, parity, partials, nb, st);
   }
   return hipGetLastError();
 }
@@ -1255,13 +1414,16 @@ OMM_BETA_DIRECTION(double, float, double)
 OMM_BETA_DIRECTION(double, float, float)
 #undef OMM_BETA_DIRECTION
 
-hipError_t line_search(const double* HW, const double* SW, const double* H1, const double* S1,
-                       const double* H2, const double* S2, int M, double* partials, DevState* st,
-                       hipStream_t s) {
-  const int nb = tile_blocks(M);
-  hipLaunchKernelGGL(k_coef_partials, dim3(nb), dim3(NT), 0, s, HW, SW, H1, S1, H2, S2, M,
-                     partials, st);
-  hipLaunchKernelGGL(k_line_final, dim3(1), dim3(NT), 0, s, partials, nb, st);
+// With at most 256 blocks of partial sums a block can sum them in about a microsecond itself, and the
+// line minimum, the update of C, HC, SC and that of HW, SW are one launch: 17.8 us instead of 27.0 (6.5 +
+// 12.1 + 8.4) at 2048 x 384 in the BF16 scheme. Beyond, the sums (106 KB for 1024 blocks) would be
+// re-read by every block.
+bool line_fused(int M) { return pair_blocks(M) <= 256; }
+
+hipError_t line_search(const Subspace& m, double* partials, DevState* st, bool fused, hipStream_t s) {
+  const int nb = pair_blocks(m.M);
+  hipLaunchKernelGGL(k_coef_sym, dim3(nb), dim3(NT), 0, s, m, partials, st);
+  if (!fused) hipLaunchKernelGGL(k_line_final, dim3(1), dim3(NT), 0, s, partials, nb, st);
   return hipGetLastError();
 }
 
@@ -1280,17 +1442,24 @@ OMM_UPDATE(float, float)
 OMM_UPDATE(double, float)
 #undef OMM_UPDATE
 
+namespace {
+// Whether k_update_split_mn2 may take the arrays: an even number of columns, aligned pairs.
+template <typename T, typename TD>
+bool split_wide(const T* C, const unsigned short* Dh, int64_t ldd, const T* HC, const TD* HD, const T* SC,
+                const TD* SD, int cols, const StatePlanes& p) {
+  return cols % 2 == 0 && p.ld % 2 == 0 && p.ldt % 2 == 0 && ldd % 2 == 0 && (uintptr_t)Dh % 4 == 0 &&
+         ((uintptr_t)C | (uintptr_t)HC | (uintptr_t)SC) % (2 * sizeof(T)) == 0 &&
+         ((uintptr_t)HD | (uintptr_t)SD) % (2 * sizeof(TD)) == 0;
+}
+}  // namespace
+
 template <typename T, typename TD>
 hipError_t update_coefficients_split(T* C, const unsigned short* Dh, int64_t ldd, T* HC,
                                      const TD* HD, T* SC, const TD* SD, int rows, int cols,
                                      const StatePlanes& p, const DevState* st, hipStream_t s) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
   if (!Dh || ldd < cols || p.ld < cols || p.ldt < rows) return hipErrorInvalidValue;
-  const bool wide = cols % 2 == 0 && p.ld % 2 == 0 && p.ldt % 2 == 0 && ldd % 2 == 0 &&
-                    (uintptr_t)Dh % 4 == 0 &&
-                    ((uintptr_t)C | (uintptr_t)HC | (uintptr_t)SC) % (2 * sizeof(T)) == 0 &&
-                    ((uintptr_t)HD | (uintptr_t)SD) % (2 * sizeof(TD)) == 0;
-  if (wide)
+  if (split_wide<T, TD>(C, Dh, ldd, HC, HD, SC, SD, cols, p))
     hipLaunchKernelGGL((k_update_split_mn2<T, TD>), dim3((cols + 63) / 64, (rows + 63) / 64),
                        dim3(NT), 0, s, C, Dh, ldd, HC, HD, SC, SD, rows, cols, p, st);
   else
@@ -1308,16 +1477,60 @@ OMM_UPDATE_SPLIT(float, float)
 OMM_UPDATE_SPLIT(double, float)
 #undef OMM_UPDATE_SPLIT
 
-hipError_t update_subspace(double* HW, double* SW, const double* H1, const double* S1,
-                           const double* H2, const double* S2, int M, double* partials,
-                           DevState* st, double* trace, hipStream_t s) {
-  const int T = (M + 31) / 32, npairs = T * (T + 1) / 2;
-  const int nb = npairs < RED_BLOCKS ? npairs : RED_BLOCKS;
-  hipLaunchKernelGGL(k_update_mm_sym, dim3(nb), dim3(NT), 0, s, HW, SW, H1, S1, H2, S2, M, partials,
-                     st);
-  hipLaunchKernelGGL(k_update_final, dim3(1), dim3(NT), 0, s, partials, nb, M, st, trace);
+hipError_t update_subspace(const Subspace& m, double* partials, DevState* st, double* trace, hipStream_t s) {
+  const int nb = pair_blocks(m.M);
+  hipLaunchKernelGGL(k_update_mm_sym, dim3(nb), dim3(NT), 0, s, m, partials, st);
+  hipLaunchKernelGGL(k_update_final, dim3(1), dim3(NT), 0, s, partials, nb, m.M, st, trace);
   return hipGetLastError();
 }
+
+template <typename T, typename TD>
+hipError_t update_line(T* C, const T* D, T* HC, const TD* HD, T* SC, const TD* SD, int64_t n,
+                       const Subspace& m, const double* lpart, double* epart, DevState* st,
+                       double* trace, hipStream_t s) {
+  const int nmm = pair_blocks(m.M);
+  const int nmn = (int)std::min<int64_t>((n + NT - 1) / NT, 512);
+  hipLaunchKernelGGL((k_update_line<T, TD>), dim3(nmm + nmn), dim3(NT), 0, s, C, D, HC, HD, SC, SD, n, m,
+                     nmm, lpart, nmm, epart, st);
+  hipLaunchKernelGGL(k_update_final, dim3(1), dim3(NT), 0, s, epart, nmm, m.M, st, trace);
+  return hipGetLastError();
+}
+#define OMM_UPDATE_LINE(T, TD)                                                                   \
+  template hipError_t update_line<T, TD>(T*, const T*, T*, const TD*, T*, const TD*, int64_t,    \
+                                         const Subspace&, const double*, double*, DevState*,     \
+                                         double*, hipStream_t);
+OMM_UPDATE_LINE(double, double)
+OMM_UPDATE_LINE(float, float)
+OMM_UPDATE_LINE(double, float)
+#undef OMM_UPDATE_LINE
+
+template <typename T, typename TD>
+hipError_t update_split_line(T* C, const unsigned short* Dh, int64_t ldd, T* HC, const TD* HD, T* SC,
+                             const TD* SD, int rows, int cols, const StatePlanes& p, const Subspace& m,
+                             const double* lpart, double* epart, DevState* st, double* trace,
+                             hipStream_t s) {
+  if (rows <= 0 || cols <= 0) return hipSuccess;
+  if (!split_wide<T, TD>(C, Dh, ldd, HC, HD, SC, SD, cols, p)) {
+    hipLaunchKernelGGL(k_line_final, dim3(1), dim3(NT), 0, s, lpart, pair_blocks(m.M), st);
+    const hipError_t e = update_coefficients_split<T, TD>(C, Dh, ldd, HC, HD, SC, SD, rows, cols, p, st, s);
+    return e != hipSuccess ? e : update_subspace(m, epart, st, trace, s);
+  }
+  if (!Dh || ldd < cols || p.ld < cols || p.ldt < rows) return hipErrorInvalidValue;
+  const int nmm = pair_blocks(m.M), tiles = ((cols + 63) / 64) * ((rows + 63) / 64);
+  hipLaunchKernelGGL((k_update_split_line<T, TD>), dim3(nmm + tiles), dim3(NT), 0, s, C, Dh, ldd, HC, HD, SC,
+                     SD, rows, cols, p, m, nmm, lpart, nmm, epart, st);
+  hipLaunchKernelGGL(k_update_final, dim3(1), dim3(NT), 0, s, epart, nmm, m.M, st, trace);
+  return hipGetLastError();
+}
+#define OMM_UPDATE_SPLIT_LINE(T, TD)                                                             \
+  template hipError_t update_split_line<T, TD>(T*, const unsigned short*, int64_t, T*, const TD*, T*, \
+                                               const TD*, int, int, const StatePlanes&,          \
+                                               const Subspace&, const double*, double*,          \
+                                               DevState*, double*, hipStream_t);
+OMM_UPDATE_SPLIT_LINE(double, double)
+OMM_UPDATE_SPLIT_LINE(float, float)
+OMM_UPDATE_SPLIT_LINE(double, float)
+#undef OMM_UPDATE_SPLIT_LINE
 
 hipError_t group_energy_init(const SysDev* d_sys, int nsys, hipStream_t s) {
   hipLaunchKernelGGL(g_energy_partials, dim3(GROUP_BLOCKS, nsys), dim3(NT), 0, s, d_sys);
@@ -1327,7 +1540,6 @@ hipError_t group_energy_init(const SysDev* d_sys, int nsys, hipStream_t s) {
 
 hipError_t group_direction(const SysDev* d_sys, int nsys, int parity, int first, hipStream_t s) {
   hipLaunchKernelGGL(g_pr_partials, dim3(GROUP_BLOCKS, nsys), dim3(NT), 0, s, d_sys, parity, first);
-  hipLaunchKernelGGL(g_pr_final, dim3(1, nsys), dim3(NT), 0, s, d_sys, first);
   hipLaunchKernelGGL(g_direction, dim3(4 * GROUP_BLOCKS, nsys), dim3(NT), 0, s, d_sys, parity, first);
   return hipGetLastError();
 }
