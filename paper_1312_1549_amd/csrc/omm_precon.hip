@@ -70,16 +70,34 @@ __global__ __launch_bounds__(256) void k_sweep_write(double* A, int64_t n, int64
   }
 }
 
-// The b x b blocks (b <= NB = 128) below are worked by 256 threads in registers: thread (ti, tj) holds
-// the 8 x 8 elements of rows ti + 16 a and columns tj + 16 c. The elimination is a chain of b
-// dependent steps, so what counts is the latency of one: LDS carries a step's pivot column and row
-// (BLK_LD doubles per ti or tj: 16-byte aligned, on different banks), and the loop over c is
-// unrolled, so that every register index is known.
-constexpr int BLK_LD = 10;
+// The b x b blocks (b <= NB = 128) below are worked by 512 threads in registers: thread (ti, tj) holds
+// the 8 x 4 elements of rows ti + 16 a and columns tj + 32 c. The elimination is a chain of b
+// dependent steps, so what counts is the latency of one: LDS carries a step's pivot column (COL_LD
+// doubles per ti: 16-byte aligned, on different banks) and row, the register indices are known at
+// compile time, the next pivot column is updated and published before the rest, and reciprocals
+// are two Newton steps on the hardware's estimate (full FP64 accuracy, a third of the latency of a
+// division).
+constexpr int COL_LD = 10;
 
-__device__ __forceinline__ void blk_read(double (&v)[8], const double* src) {
+__device__ __forceinline__ double recip(double d) {
+  double x = __builtin_amdgcn_rcp(d);
+  x = fma(x, fma(-d, x, 1.0), x);
+  return fma(x, fma(-d, x, 1.0), x);
+}
+// 1 / sqrt(d) and sqrt(d)
+__device__ __forceinline__ double recip_sqrt(double d, double* root) {
+  double x = __builtin_amdgcn_rsq(d);
+  x = fma(0.5 * x, fma(-d * x, x, 1.0), x);
+  x = fma(0.5 * x, fma(-d * x, x, 1.0), x);
+  const double r = d * x;
+  *root = fma(fma(-r, r, d), 0.5 * x, r);
+  return x;
+}
+
+template <int N>
+__device__ __forceinline__ void read_pairs(double (&v)[N], const double* src) {
 #pragma unroll
-  for (int k = 0; k < 8; k += 2) {
+  for (int k = 0; k < N; k += 2) {
     const double2 q = *reinterpret_cast<const double2*>(src + k);
     v[k] = q.x;
     v[k + 1] = q.y;
@@ -98,96 +116,115 @@ __device__ __forceinline__ unsigned row16_max(unsigned v) {
 // In-place inverse of W by Gauss-Jordan with partial row pivoting. Step p eliminates column p with
 // the row r of largest |W[r][p]| (to 13 bits of the mantissa) among the rows not used yet; no row
 // is moved: row r of the eliminated matrix is row p of the inverse, and its column q is column
-// r_q. Two barriers a step: the pivot column, in which every wave finds the pivot for itself (its
-// 16 row groups hold all rows), and the pivot row. A zero or non-finite pivot sets *bad.
-// 188 us for a 128 x 128 block (five barriers a step and exchanged rows took 560 us).
-__global__ __launch_bounds__(256) void k_small_gj(double* W, int b, int* bad) {
-  __shared__ __attribute__((aligned(16))) double colp[16 * BLK_LD], rowp[16 * BLK_LD];
+// r_q. Two barriers a step: the pivot column with the row its 16 owners chose, and the pivot row. A
+// zero or non-finite pivot sets *bad.
+// 128 x 128: 138 us (five barriers a step and exchanged rows took 560 us).
+__global__ __launch_bounds__(512) void k_small_gj(double* W, int b, int* bad) {
+  __shared__ __attribute__((aligned(16))) double colp[16 * COL_LD], rowp[NB];
+  __shared__ int pivot;
   __shared__ int row_of[NB], step_of[NB];  // pivot row of a step, step of a row
   const int tid = threadIdx.x, ti = tid & 15, tj = tid >> 4;
-  double w[8][8];
+  double w[8][4];
   unsigned used = 0;  // bit a: row ti + 16 a is not a candidate
 #pragma unroll
   for (int a = 0; a < 8; ++a) {
     if (ti + 16 * a >= b) used |= 1u << a;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int i = ti + 16 * a, j = tj + 16 * c;
+    for (int c = 0; c < 4; ++c) {
+      const int i = ti + 16 * a, j = tj + 32 * c;
       w[a][c] = i < b && j < b ? W[i * b + j] : 0.0;
     }
   }
+  // the owners of a column (16 lanes, all rows) publish it and its pivot row
+  auto publish_column = [&](auto cc) __attribute__((always_inline)) {
+    constexpr int C = decltype(cc)::value;
+    unsigned key = 0;
 #pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    for (int s = 0; s < 16; ++s) {
-      const int p = 16 * c + s;
+    for (int a = 0; a < 8; ++a) {
+      colp[ti * COL_LD + a] = w[a][C];
+      const unsigned hi = (unsigned)__double2hiint(w[a][C]) & 0x7fffff80u;
+      key = max(key, (used >> a & 1) ? 0u : (0x80000000u | hi | (unsigned)(127 - (ti + 16 * a))));
+    }
+    key = row16_max(key);
+    if (ti == 0) pivot = 127 - (int)(key & 127u);
+  };
+  if (tj == 0) publish_column(std::integral_constant<int, 0>{});
+  auto columns = [&](auto cc) __attribute__((always_inline)) {
+    constexpr int C = decltype(cc)::value, CN = C < 3 ? C + 1 : C;
+    for (int s = 0; s < 32; ++s) {
+      const int p = 32 * C + s;
       if (p >= b) break;
-      if (tj == s)
-#pragma unroll
-        for (int a = 0; a < 8; ++a) colp[ti * BLK_LD + a] = w[a][c];
       __syncthreads();
+      const int r = __builtin_amdgcn_readfirstlane(pivot), tr = r & 15;
+      const double d = colp[tr * COL_LD + (r >> 4)];
       double ca[8];
-      blk_read(ca, colp + ti * BLK_LD);
-      unsigned key = 0;
-#pragma unroll
-      for (int a = 0; a < 8; ++a) {
-        const unsigned hi = (unsigned)__double2hiint(ca[a]) & 0x7fffff80u;
-        const unsigned k = (used >> a & 1) ? 0u : (0x80000000u | hi | (unsigned)(127 - (ti + 16 * a)));
-        key = max(key, k);
-      }
-      key = (unsigned)__builtin_amdgcn_readfirstlane((int)row16_max(key));
-      const int r = 127 - (int)(key & 127u), tr = r & 15;
-      const double d = colp[tr * BLK_LD + (r >> 4)];
+      read_pairs<8>(ca, colp + ti * COL_LD);
       // the pivot row goes out and its elements become 0 - (-1) (row / d)
-      auto publish = [&](auto ac) {
+      auto publish_row = [&](auto ac) __attribute__((always_inline)) {
         constexpr int A = decltype(ac)::value;
         if (ti == tr) {
 #pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            rowp[tj * BLK_LD + k] = w[A][k];
+          for (int k = 0; k < 4; ++k) {
+            rowp[tj * 4 + k] = w[A][k];
             w[A][k] = 0.0;
           }
           ca[A] = -1.0;
           used |= 1u << A;
         }
+        asm volatile("; rows 16 * %0" ::"n"(A));  // keeps the cases apart: merged, they index w at run time
       };
       switch (r >> 4) {
-        case 0: publish(std::integral_constant<int, 0>{}); break;
-        case 1: publish(std::integral_constant<int, 1>{}); break;
-        case 2: publish(std::integral_constant<int, 2>{}); break;
-        case 3: publish(std::integral_constant<int, 3>{}); break;
-        case 4: publish(std::integral_constant<int, 4>{}); break;
-        case 5: publish(std::integral_constant<int, 5>{}); break;
-        case 6: publish(std::integral_constant<int, 6>{}); break;
-        default: publish(std::integral_constant<int, 7>{}); break;
+        case 0: publish_row(std::integral_constant<int, 0>{}); break;
+        case 1: publish_row(std::integral_constant<int, 1>{}); break;
+        case 2: publish_row(std::integral_constant<int, 2>{}); break;
+        case 3: publish_row(std::integral_constant<int, 3>{}); break;
+        case 4: publish_row(std::integral_constant<int, 4>{}); break;
+        case 5: publish_row(std::integral_constant<int, 5>{}); break;
+        case 6: publish_row(std::integral_constant<int, 6>{}); break;
+        default: publish_row(std::integral_constant<int, 7>{}); break;
       }
-      const double ip = 1.0 / d;
+      const double ip = recip(d);
       if (tid == 0) {
         row_of[p] = r;
         step_of[r] = p;
-        if (!(fabs(d) > 0.0) || !isfinite(d)) atomicOr(bad, 1);
+        if (!(fabs(d) > 0.0) || !isfinite(ip)) atomicOr(bad, 1);
       }
       __syncthreads();
-      double rr[8];
-      blk_read(rr, rowp + tj * BLK_LD);
+      double rr[4];
+      read_pairs<4>(rr, rowp + tj * 4);
 #pragma unroll
-      for (int k = 0; k < 8; ++k) rr[k] *= ip;
+      for (int k = 0; k < 4; ++k) rr[k] *= ip;
       if (tj == s) {  // the pivot column: 0 - c_i / d
-        rr[c] = ip;
+        rr[C] = ip;
 #pragma unroll
-        for (int a = 0; a < 8; ++a) w[a][c] = 0.0;
+        for (int a = 0; a < 8; ++a) w[a][C] = 0.0;
+      }
+      auto eliminate = [&](int k) __attribute__((always_inline)) {
+#pragma unroll
+        for (int a = 0; a < 8; ++a) w[a][k] = fma(-ca[a], rr[k], w[a][k]);
+      };
+      eliminate(C);
+      if (CN != C) eliminate(CN);
+      if (s < 31) {
+        if (tj == s + 1) publish_column(std::integral_constant<int, C>{});
+      } else if (CN != C) {
+        if (tj == 0) publish_column(std::integral_constant<int, CN>{});
       }
 #pragma unroll
-      for (int a = 0; a < 8; ++a)
-#pragma unroll
-        for (int k = 0; k < 8; ++k) w[a][k] = fma(-ca[a], rr[k], w[a][k]);
+      for (int k = 0; k < 4; ++k)
+        if (k != C && k != CN) eliminate(k);
     }
-  }
+  };
+  columns(std::integral_constant<int, 0>{});
+  columns(std::integral_constant<int, 1>{});
+  columns(std::integral_constant<int, 2>{});
+  columns(std::integral_constant<int, 3>{});
   __syncthreads();
 #pragma unroll
   for (int a = 0; a < 8; ++a)
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int i = ti + 16 * a, j = tj + 16 * c;
+    for (int c = 0; c < 4; ++c) {
+      const int i = ti + 16 * a, j = tj + 32 * c;
       if (i < b && j < b) W[step_of[i] * b + row_of[j]] = w[a][c];
     }
 }
@@ -225,70 +262,99 @@ __global__ __launch_bounds__(1024) void k_maxabs(const double* Z, int64_t total,
 // barrier a step, the published column and row being double-buffered. Entries of a column above
 // its diagonal are published as zeros, so finished rows and columns take no updates. A pivot that is
 // not positive and finite sets *bad (the block is then garbage, never used).
-// 128 x 128: 92 us (the factorization in LDS and a forward substitution through memory took 1104).
-__global__ __launch_bounds__(256) void k_chol_block(const double* A, double* L, double* Linv, int64_t n,
+// 128 x 128: 86 us (the factorization in LDS and a forward substitution through memory took 1104).
+__global__ __launch_bounds__(512) void k_chol_block(const double* A, double* L, double* Linv, int64_t n,
                                                     int64_t k0, int b, double* W, int* bad) {
-  __shared__ __attribute__((aligned(16))) double colp[2][16 * BLK_LD], rowx[2][16 * BLK_LD];
+  __shared__ __attribute__((aligned(16))) double colp[2][16 * COL_LD], rowx[2][NB];
   const int tid = threadIdx.x, ti = tid & 15, tj = tid >> 4;
-  double l[8][8], x[8][8];
+  double l[8][4], x[8][4];
 #pragma unroll
   for (int a = 0; a < 8; ++a)
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int i = ti + 16 * a, j = tj + 16 * c;
+    for (int c = 0; c < 4; ++c) {
+      const int i = ti + 16 * a, j = tj + 32 * c;
       l[a][c] = i < b && j < b ? A[(k0 + i) * n + k0 + j] : 0.0;
       x[a][c] = i == j ? 1.0 : 0.0;
     }
+  // column j of the remaining matrix and row j of x, j = 16 O + s
+  auto publish = [&](auto oc, int s, int buf) __attribute__((always_inline)) {
+    constexpr int O = decltype(oc)::value;
+    const int j = 16 * O + s;
+    if (tj == (j & 31))
 #pragma unroll
-  for (int o = 0; o < 8; ++o) {
+      for (int a = 0; a < 8; ++a) colp[buf][ti * COL_LD + a] = ti + 16 * a >= j ? l[a][O / 2] : 0.0;
+    if (ti == s)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        rowx[buf][tj * 4 + c] = x[O][c];
+        x[O][c] = 0.0;
+      }
+  };
+  publish(std::integral_constant<int, 0>{}, 0, 0);
+  auto steps = [&](auto oc) __attribute__((always_inline)) {
+    constexpr int O = decltype(oc)::value, C = O / 2, ON = O < 7 ? O + 1 : O;
     for (int s = 0; s < 16; ++s) {
-      const int j = 16 * o + s, buf = s & 1;
+      const int j = 16 * O + s, buf = s & 1;
       if (j >= b) break;
-      if (tj == s)
-#pragma unroll
-        for (int a = 0; a < 8; ++a) colp[buf][ti * BLK_LD + a] = ti + 16 * a >= j ? l[a][o] : 0.0;
-      if (ti == s)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          rowx[buf][tj * BLK_LD + c] = x[o][c];
-          x[o][c] = 0.0;
-        }
       __syncthreads();
-      double ca[8], cb[8], xr[8];
-      blk_read(ca, colp[buf] + ti * BLK_LD);
-      blk_read(cb, colp[buf] + tj * BLK_LD);
-      blk_read(xr, rowx[buf] + tj * BLK_LD);
-      double d = colp[buf][s * BLK_LD + o];
+      double ca[8], cb[4], xr[4];
+      double d = colp[buf][s * COL_LD + O];
+      read_pairs<8>(ca, colp[buf] + ti * COL_LD);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) cb[c] = colp[buf][(tj & 15) * COL_LD + (tj >> 4) + 2 * c];
+      read_pairs<4>(xr, rowx[buf] + tj * 4);
       if (!(d > 0.0) || !isfinite(d)) {
         if (tid == 0) atomicOr(bad, 1);
         d = 1.0;
       }
-      const double p = sqrt(d), ip = 1.0 / p;
+      double p;
+      const double ip = recip_sqrt(d, &p);
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        ca[k] *= ip;
+      for (int k = 0; k < 8; ++k) ca[k] *= ip;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
         cb[k] *= ip;
         xr[k] *= ip;
       }
+      const double co = ti == s ? -1.0 : ca[O];  // row j of x: 0 - (-1) (row / p)
+      auto update_l = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
-      for (int a = o; a < 8; ++a)
+        for (int a = O; a < 8; ++a) l[a][c] = fma(-ca[a], cb[c], l[a][c]);
+      };
+      auto update_x = [&](int a) __attribute__((always_inline)) {
 #pragma unroll
-        for (int c = o; c < 8; ++c) l[a][c] = fma(-ca[a], cb[c], l[a][c]);
-      if (tj == s)  // column j of L
+        for (int c = 0; c <= C; ++c) x[a][c] = fma(a == O ? -co : -ca[a], xr[c], x[a][c]);
+      };
+      // what step j + 1 needs first
+      update_l(C);
+      if (ON / 2 != C) update_l(ON / 2);
+      update_x(O);
+      if (ON != O) update_x(ON);
+      if (tj == (j & 31))  // column j of L
 #pragma unroll
-        for (int a = 0; a < 8; ++a) l[a][o] = ti + 16 * a == j ? p : ca[a];
-      if (ti == s) ca[o] = -1.0;  // row j of x: 0 - (-1) (row / p)
+        for (int a = 0; a < 8; ++a) l[a][C] = ti + 16 * a == j ? p : ca[a];
+      if (s < 15) publish(std::integral_constant<int, O>{}, s + 1, buf ^ 1);
+      else if (ON != O) publish(std::integral_constant<int, ON>{}, 0, buf ^ 1);
 #pragma unroll
-      for (int a = o; a < 8; ++a)
+      for (int c = C + 1; c < 4; ++c)
+        if (c != ON / 2) update_l(c);
 #pragma unroll
-        for (int c = 0; c <= o; ++c) x[a][c] = fma(-ca[a], xr[c], x[a][c]);
+      for (int a = O + 2; a < 8; ++a) update_x(a);
     }
-  }
+  };
+  steps(std::integral_constant<int, 0>{});
+  steps(std::integral_constant<int, 1>{});
+  steps(std::integral_constant<int, 2>{});
+  steps(std::integral_constant<int, 3>{});
+  steps(std::integral_constant<int, 4>{});
+  steps(std::integral_constant<int, 5>{});
+  steps(std::integral_constant<int, 6>{});
+  steps(std::integral_constant<int, 7>{});
 #pragma unroll
   for (int a = 0; a < 8; ++a)
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int i = ti + 16 * a, j = tj + 16 * c;
+    for (int c = 0; c < 4; ++c) {
+      const int i = ti + 16 * a, j = tj + 32 * c;
       if (i < b && j < b) {
         L[(k0 + i) * n + k0 + j] = j <= i ? l[a][c] : 0.0;
         W[i * b + j] = Linv[(k0 + i) * n + k0 + j] = j <= i ? x[a][c] : 0.0;
@@ -371,7 +437,7 @@ hipError_t invert_symmetric(double* A, int64_t n, double* work, hipStream_t s, i
   for (int64_t k0 = 0; k0 < n; k0 += NB) {
     const int b = (int)((n - k0) < NB ? (n - k0) : NB);
     hipLaunchKernelGGL(k_panel, ew_grid(n * b), dim3(256), 0, s, A, n, k0, b, U, W);
-    hipLaunchKernelGGL(k_small_gj, dim3(1), dim3(256), 0, s, W, b, flag);
+    hipLaunchKernelGGL(k_small_gj, dim3(1), dim3(512), 0, s, W, b, flag);
     TRYHIP(hipGetLastError());
     if (n > b) {
       TRYHIP(product(N, b, b, U, b, KC, W, b, RC, V, b, 1.0, nullptr, 0.0, 0, 0, s));    // V = U W
@@ -435,7 +501,7 @@ hipError_t cholesky_and_inverse(double* A, double* L, double* Linv, int64_t n, d
   hipLaunchKernelGGL(k_zero, ew_grid(n * n), dim3(256), 0, s, Linv, n * n);
   for (int64_t k0 = 0; k0 < n; k0 += NB) {
     const int b = (int)((n - k0) < NB ? (n - k0) : NB);
-    hipLaunchKernelGGL(k_chol_block, dim3(1), dim3(256), 0, s, A, L, Linv, n, k0, b, W, flag);
+    hipLaunchKernelGGL(k_chol_block, dim3(1), dim3(512), 0, s, A, L, Linv, n, k0, b, W, flag);
     TRYHIP(hipGetLastError());
     if (k0 > 0) {
       const int K = (int)k0;
