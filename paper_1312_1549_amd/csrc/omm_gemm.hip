@@ -19,22 +19,41 @@ grouped_fn pick_grouped_f32(const GemmDesc& d);
 grouped_fn pick_grouped_f64(const GemmDesc& d);
 
 namespace {
-template <typename TC, typename TX>
+// Sums the split-K partials (type TP: that of the accumulators) in split order, FP64, and applies the
+// epilogue: four columns per thread, rows blockIdx.y, blockIdx.y + gridDim.y, ..
+template <typename TC, typename TX, typename TP>
 __global__ __launch_bounds__(256) void splitk_reduce(GemmBatch batch, const int* done, int nsplit,
-                                                     const double* ws) {
+                                                     const TP* ws) {
   if (done && *done) return;
-  const GemmOp& op = batch.op[blockIdx.y];
-  const int64_t mn = (int64_t)op.M * op.N;
-  const int nops = gridDim.y;
-  for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < mn;
-       idx += (int64_t)gridDim.x * 256) {
-    double s = 0.0;
-    const int row = (int)(idx / op.N), col = (int)(idx % op.N);
-    if (op.tri && row > col) continue;  // mirrored afterwards (its tile may not have run)
-    for (int sp = 0; sp < nsplit; ++sp) s += ws[((int64_t)sp * nops + blockIdx.y) * mn + idx];
-    double v = op.alpha * s;
-    if (op.X) v += op.beta * (double)ldg<TX>(op.X, (int64_t)row * op.ldx + col);
-    store_out<TC>(op, row, col, v);
+  typedef TP P4 __attribute__((ext_vector_type(4)));
+  const GemmOp& op = batch.op[blockIdx.z];
+  const int64_t mn = (int64_t)op.M * op.N, step = mn * gridDim.z;
+  const int c0 = (blockIdx.x * 256 + threadIdx.x) * 4;
+  if (c0 >= op.N) return;
+  const bool whole = op.N % 4 == 0;  // rows of partials start on 4-element boundaries
+  for (int row = blockIdx.y; row < op.M; row += gridDim.y) {
+    if (op.tri && row > c0 + 3) continue;  // below the diagonal: its tile may not have run
+    const TP* p = ws + (int64_t)blockIdx.z * mn + (int64_t)row * op.N + c0;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int sp = 0; sp < nsplit; ++sp, p += step) {
+      if (whole) {
+        const P4 v = *reinterpret_cast<const P4*>(p);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] += (double)v[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (c0 + e < op.N) s[e] += (double)p[e];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int col = c0 + e;
+      if (col >= op.N || (op.tri && row > col)) continue;
+      double v = op.alpha * s[e];
+      if (op.X) v += op.beta * (double)ldg<TX>(op.X, (int64_t)row * op.ldx + col);
+      store_out<TC>(op, row, col, v);
+    }
   }
 }
 // C[i][j] = C[j][i] for i > j of every symmetric (tri) product: 32 x 32 blocks on and below the
@@ -86,14 +105,17 @@ __global__ __launch_bounds__(256) void pair_fill(GemmBatch batch, const int* don
 
 using namespace gemm_detail;
 
-size_t gemm_splitk_ws_bytes(const GemmOp* ops, int nops, int splitk) {
-  if (splitk <= 1) return 0;
-  return (size_t)splitk * nops * (size_t)ops[0].M * ops[0].N * sizeof(double);
+namespace {
+// split-K partials in the accumulators' type
+size_t splitk_ws_bytes(const GemmDesc& d, const GemmOp* ops, int nops) {
+  if (d.splitk <= 1) return 0;
+  return (size_t)d.splitk * nops * (size_t)ops[0].M * ops[0].N * (d.compute == CF64 ? sizeof(double) : sizeof(float));
 }
+}  // namespace
 
 size_t gemm_ws_bytes(const GemmDesc& d, const GemmOp* ops, int nops) {
   if (d.tile == 6) return (size_t)2 * SK_GRID * DMA_BM * DMA_BN * sizeof(float);
-  return gemm_splitk_ws_bytes(ops, nops, d.splitk);
+  return splitk_ws_bytes(d, ops, nops);
 }
 
 int gemm_num_tiles() { return NTILES; }
@@ -276,7 +298,7 @@ hipError_t launch_products(const GemmDesc& d, const GemmOp* ops, int nops, const
   const int tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
   const int per = (tiles + 7) / 8;
   const int splitk = dd.splitk > 1 ? dd.splitk : 1;
-  if (splitk > 1 && (!ws || ws_bytes < gemm_splitk_ws_bytes(ops, nops, splitk)))
+  if (splitk > 1 && (!ws || ws_bytes < splitk_ws_bytes(dd, ops, nops)))
     return hipErrorInvalidValue;
   // small tiles of symmetric or triangular products are dealt in short runs
   bool dealt = false;
@@ -285,14 +307,18 @@ hipError_t launch_products(const GemmDesc& d, const GemmOp* ops, int nops, const
   hipLaunchKernelGGL(fn, grid, dim3(tile_threads(dd.tile, dd.compute)), 0, s, b, done, splitk, ws);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splitk == 1) return e;
-  const int64_t mn = (int64_t)M * N;
-  int blocks = (int)((mn + 255) / 256);
-  if (blocks > 4096) blocks = 4096;
-  dim3 rgrid(blocks, nops);
-  void (*red)(GemmBatch, const int*, int, const double*) = nullptr;
-  if (dd.tc == T_F64) red = dd.tx == T_F64 ? splitk_reduce<double, double> : splitk_reduce<double, float>;
-  else red = dd.tx == T_F64 ? splitk_reduce<float, double> : splitk_reduce<float, float>;
-  hipLaunchKernelGGL(red, rgrid, dim3(256), 0, s, b, done, splitk, (const double*)ws);
+  // blocks of 1024 columns, rows dealt so that a few thousand blocks run
+  const int bx = (N + 1023) / 1024;
+  const dim3 rgrid(bx, std::min(M, std::max(1, 4096 / (bx * nops))), nops);
+  auto reduce = [&](auto* partials) {
+    typedef typename std::remove_pointer<decltype(partials)>::type TP;
+    void (*red)(GemmBatch, const int*, int, const TP*) =
+        dd.tc == T_F64 ? (dd.tx == T_F64 ? splitk_reduce<double, double, TP> : splitk_reduce<double, float, TP>)
+                       : (dd.tx == T_F64 ? splitk_reduce<float, double, TP> : splitk_reduce<float, float, TP>);
+    hipLaunchKernelGGL(red, rgrid, dim3(256), 0, s, b, done, splitk, (const TP*)partials);
+  };
+  if (dd.compute == CF64) reduce(ws);
+  else reduce(reinterpret_cast<float*>(ws));
   return hipGetLastError();
 }
 }  // namespace

@@ -404,12 +404,13 @@ __device__ __forceinline__ void store_out(const GemmOp& op, int row, int col, do
   }
 }
 
-// Epilogue of one wave's TM x TN blocks at (r0, c0): C = alpha acc + beta X, or the FP64 split-K
-// partial at ws[(sp * nops + z) * M * N + ...].
+// Epilogue of one wave's TM x TN blocks at (r0, c0): C = alpha acc + beta X, or the split-K partial
+// (the accumulator as it is) at ws[(sp * nops + z) * M * N + ...].
 template <int MODE, typename TC, typename TX, int TM, int TN, typename acc_t>
 __device__ __forceinline__ void store_acc(const GemmOp& op, const acc_t (&acc)[TM][TN], int r0,
-                                          int c0, int lane, int sp, int nsplit, double* ws, int z,
+                                          int c0, int lane, int sp, int nsplit, void* ws, int z,
                                           int nops) {
+  typedef typename std::conditional<MODE == CF64, double, float>::type part_t;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -422,7 +423,8 @@ __device__ __forceinline__ void store_acc(const GemmOp& op, const acc_t (&acc)[T
         if (row < op.M && col < op.N) {
           const double s = (double)acc[i][j][r];
           if (nsplit > 1) {
-            ws[((int64_t)sp * nops + z) * op.M * op.N + (int64_t)row * op.N + col] = s;
+            static_cast<part_t*>(ws)[((int64_t)sp * nops + z) * op.M * op.N + (int64_t)row * op.N + col] =
+                acc[i][j][r];
           } else {
             double v = op.alpha * s;
             if (op.X) v += op.beta * (double)ldg<TX>(op.X, (int64_t)row * op.ldx + col);

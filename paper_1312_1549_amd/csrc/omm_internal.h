@@ -90,10 +90,9 @@ struct GemmDesc {
 };
 
 // Launch up to 4 GEMMs that share a descriptor (one launch; blockIdx.z selects the op).
-// `done` (nullable) makes the launch a no-op when *done != 0. `ws` is FP64 scratch for split-K.
+// `done` (nullable) makes the launch a no-op when *done != 0. `ws` is scratch for split-K partials.
 hipError_t gemm_launch(const GemmDesc& d, const GemmOp* ops, int nops, const int* done,
                        double* ws, size_t ws_bytes, hipStream_t s);
-size_t gemm_splitk_ws_bytes(const GemmOp* ops, int nops, int splitk);
 // Workspace a launch with descriptor d needs (split-K partials, or stream-K tile parts).
 size_t gemm_ws_bytes(const GemmDesc& d, const GemmOp* ops, int nops);
 // Block pattern of the block-sparse B lists: 256-wide column tiles of the direct-to-LDS GEMM,
