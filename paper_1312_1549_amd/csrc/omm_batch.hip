@@ -56,13 +56,18 @@ struct OpList {
   const int** d_done = nullptr;
   int cap = 0;
   std::vector<int> tile_start;  // tile prefix sums (host copy, kept until the upload has run)
+  std::vector<GemmOp> on_device;  // the list as uploaded
+  std::vector<const int*> done_on_device;
 };
 
 }  // namespace
 
-// The grouped products of one phase's CG stages.
+// The grouped products of one phase's CG stages, and the captured graph of two line searches, kept while
+// the lists stay what they were.
 struct PhaseLists {
   OpList init1, init2, grad[2], pg[2], hdsd, proj;
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;
   std::vector<OpList*> all() {
     return {&init1, &init2, &grad[0], &grad[1], &pg[0], &pg[1], &hdsd, &proj};
   }
@@ -80,8 +85,6 @@ struct omm_batch {
   int* d_cmp = nullptr;  // change flag of omm_batch_set_HS's S / T comparison, then the two
                          // flags (non-finite, asymmetric) of the device-input validation
   PhaseLists L32, L64;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
   int mode = OMM_FP32;  // OMM_FP32 or OMM_FP64
   bool refine = false;  // OMM_FP32: FP64 phase after the FP32 one
   double mixed_tol = 1e-9;
@@ -134,6 +137,13 @@ void free_list(OpList& L) {
   if (L.d_done) (void)hipFree((void*)L.d_done);
   L.d_done = nullptr;
   L.cap = 0;
+}
+
+void drop_graph(PhaseLists& L) {
+  if (L.exec) (void)hipGraphExecDestroy(L.exec);
+  if (L.graph) (void)hipGraphDestroy(L.graph);
+  L.exec = nullptr;
+  L.graph = nullptr;
 }
 
 void free_sys(BSys& s) {
@@ -246,9 +256,26 @@ GemmOp gop(int M, int N, int K, const void* A, int64_t lda, const void* B, int64
   return op;
 }
 
-// Picks the tile, uploads the op list and its tile prefix sums.
-int upload_list(omm_batch* b, OpList& L) {
+bool same_op(const GemmOp& x, const GemmOp& y) {
+  bool same = x.M == y.M && x.N == y.N && x.nseg == y.nseg && x.C == y.C && x.ldc == y.ldc && x.X == y.X &&
+              x.ldx == y.ldx && x.alpha == y.alpha && x.beta == y.beta && x.tri == y.tri &&
+              x.kcut == y.kcut && x.pair_rows == y.pair_rows;
+  for (int g = 0; g < 2; ++g)
+    same = same && x.A[g] == y.A[g] && x.B[g] == y.B[g] && x.lda[g] == y.lda[g] && x.ldb[g] == y.ldb[g] &&
+           x.K[g] == y.K[g];
+  return same;
+}
+
+// Picks the tile, uploads the op list and its tile prefix sums; nothing to do (`*fresh` stays) where the
+// list equals the one on the device.
+int upload_list(omm_batch* b, OpList& L, bool* fresh) {
   const int n = (int)L.ops.size();
+  if (n > 0) direct_choose(L.d, L.ops.data(), n);
+  if (L.on_device.size() == L.ops.size() && L.done == L.done_on_device &&
+      std::equal(L.ops.begin(), L.ops.end(), L.on_device.begin(), same_op))
+    return OMM_OK;
+  *fresh = true;
+  L.on_device.clear();
   if (n == 0) return OMM_OK;
   if (L.cap < n) {
     free_list(L);
@@ -258,7 +285,6 @@ int upload_list(omm_batch* b, OpList& L) {
       return bfail(b, OMM_E_ALLOC, "hipMalloc failed");
     L.cap = n;
   }
-  direct_choose(L.d, L.ops.data(), n);
   L.tile_start.assign(n + 1, 0);
   const int bm = gemm_tile_rows(L.d.tile, L.d.compute), bn = gemm_tile_cols(L.d.tile, L.d.compute);
   for (int i = 0; i < n; ++i)
@@ -269,6 +295,8 @@ int upload_list(omm_batch* b, OpList& L) {
                          hipMemcpyHostToDevice, b->stream));
   BHIP(b, hipMemcpyAsync((void*)L.d_done, L.done.data(), n * sizeof(int*), hipMemcpyHostToDevice,
                          b->stream));
+  L.on_device = L.ops;
+  L.done_on_device = L.done;
   return OMM_OK;
 }
 
@@ -282,6 +310,7 @@ int launch_list(omm_batch* b, OpList& L) {
 // Builds the op lists of every CG stage of one phase (FP32 or FP64) from the current buffers.
 int build_lists(omm_batch* b, bool f64) {
   PhaseLists& L = f64 ? b->L64 : b->L32;
+  bool fresh = false;
   for (OpList* l : L.all()) {
     l->ops.clear();
     l->done.clear();
@@ -347,9 +376,12 @@ int build_lists(omm_batch* b, bool f64) {
   for (OpList* l : L.all()) {
     if (b->cplx)
       for (GemmOp& op : l->ops) op.pair_rows = op.M;
-    BTRY(upload_list(b, *l));
+    BTRY(upload_list(b, *l, &fresh));
   }
-  BHIP(b, hipStreamSynchronize(b->stream));  // the uploads read host vectors
+  if (fresh) {
+    drop_graph(L);
+    BHIP(b, hipStreamSynchronize(b->stream));  // the uploads read host vectors
+  }
   return OMM_OK;
 }
 
@@ -365,13 +397,6 @@ int batch_iteration(omm_batch* b, PhaseLists& L, const SysDev* d_sys, int k) {
   BHIP(b, group_line_search(d_sys, n, b->stream));
   BHIP(b, group_update(d_sys, n, b->stream));
   return OMM_OK;
-}
-
-void drop_graph(omm_batch* b) {
-  if (b->exec) (void)hipGraphExecDestroy(b->exec);
-  if (b->graph) (void)hipGraphDestroy(b->graph);
-  b->exec = nullptr;
-  b->graph = nullptr;
 }
 
 int read_states(omm_batch* b) {
@@ -414,7 +439,6 @@ int run_phase(omm_batch* b, bool f64, double tol, int max_iter) {
     h.max_iter = max_iter;
   }
   BHIP(b, hipMemcpyAsync(b->st, b->st_host, n * sizeof(DevState), hipMemcpyHostToDevice, b->stream));
-  drop_graph(b);
   BTRY(upload_sysdev(b, f64));
   BTRY(build_lists(b, f64));
 
@@ -428,21 +452,23 @@ int run_phase(omm_batch* b, bool f64, double tol, int max_iter) {
   if (max_iter > 0 && !all_done) {
     BTRY(batch_iteration(b, L, d_sys, 0));
     // line searches 1 and 2 (parities 1, 0) captured once, replayed until all systems stop
-    BHIP(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-    int r1 = batch_iteration(b, L, d_sys, 1);
-    int r2 = r1 == OMM_OK ? batch_iteration(b, L, d_sys, 2) : r1;
-    hipGraph_t g = nullptr;
-    hipError_t ec = hipStreamEndCapture(b->stream, &g);
-    if (r1 != OMM_OK || r2 != OMM_OK) {
-      if (g) (void)hipGraphDestroy(g);
-      return r1 != OMM_OK ? r1 : r2;
+    if (!L.exec) {
+      BHIP(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
+      int r1 = batch_iteration(b, L, d_sys, 1);
+      int r2 = r1 == OMM_OK ? batch_iteration(b, L, d_sys, 2) : r1;
+      hipGraph_t g = nullptr;
+      hipError_t ec = hipStreamEndCapture(b->stream, &g);
+      if (r1 != OMM_OK || r2 != OMM_OK) {
+        if (g) (void)hipGraphDestroy(g);
+        return r1 != OMM_OK ? r1 : r2;
+      }
+      BHIP(b, ec);
+      L.graph = g;
+      BHIP(b, hipGraphInstantiate(&L.exec, L.graph, nullptr, nullptr, 0));
     }
-    BHIP(b, ec);
-    b->graph = g;
-    BHIP(b, hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0));
     const int launches = (max_iter + 1) / 2;
     for (int l = 0; l < launches; ++l) {
-      BHIP(b, hipGraphLaunch(b->exec, b->stream));
+      BHIP(b, hipGraphLaunch(L.exec, b->stream));
       if ((l + 1) % 4 == 0 || l + 1 == launches) {
         BTRY(read_states(b));
         all_done = true;
@@ -494,7 +520,8 @@ int omm_batch_create(int nsys, const int64_t* N, const int64_t* M, omm_batch** o
 int omm_batch_destroy(omm_batch* b) {
   if (!b) return OMM_E_ARG;
   if (b->stream) (void)hipStreamSynchronize(b->stream);
-  drop_graph(b);
+  drop_graph(b->L32);
+  drop_graph(b->L64);
   for (BSys& s : b->sys) free_sys(s);
   for (OpList* L : b->L32.all()) free_list(*L);
   for (OpList* L : b->L64.all()) free_list(*L);
@@ -571,7 +598,6 @@ int batch_set_HS(omm_batch* b, int i, const double* H, const double* S, const do
   s.have_T = T != nullptr;
   s.have_HS = true;
   if (!diff) s.p_kind = kept_kind;
-  drop_graph(b);
   return OMM_OK;
 }
 }  // namespace
