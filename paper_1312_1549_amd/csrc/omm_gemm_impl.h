@@ -1,4 +1,6 @@
-// MFMA GEMM tile loop for gfx950 (included by the per-precision translation units).
+// MFMA GEMM tile loop for gfx950 (included by the per-precision translation units): the staged tiles.
+// FP64 and FP32 products run on them only where OMM_TILE pins one and, block-sparse, on tile 4; the others
+// take the small tiles of omm_gemm_direct.h.
 //
 //   C = alpha * sum_seg A_seg * B_seg + beta * X       (up to 2 summed K segments)
 //
