@@ -22,7 +22,7 @@ struct DevState {
   int iter;          // completed line searches
   int max_iter;
   int done;          // 0 running, 1 converged, 2 max_iter, <0 error code
-  int pad;
+  int line_code;     // error code of the last line minimum (0: none); becomes `done` in a later launch
 };
 
 // Operand layout of a GEMM operand X with outer index r (row of A, column of B) and inner k:

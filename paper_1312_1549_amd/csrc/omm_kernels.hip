@@ -740,7 +740,9 @@ __device__ int line_minimum(const double* a, double* xout) {
 // The quartic of the line search from the partial sums of its 13 terms and its minimum x, in every thread
 // of the block (false: none). Wave w sums columns w, w + 4, ..; the same sums in every block that
 // calls this, so that a kernel may find x for itself; one block (`writer`) keeps the result, or the
-// error, in the state.
+// error code, in the state. It does not set `done`: the waves of a launch test that as they start, and
+// a block of which some waves saw it set in mid-launch would go on without them (thread 0 of a
+// launch of one block, or the next launch, sets it from line_code).
 __device__ __forceinline__ bool line_x(const double* partials, int nb, DevState* st, bool writer,
                                        double* xout) {
   __shared__ double s[NCOEF];
@@ -768,8 +770,8 @@ __device__ __forceinline__ bool line_x(const double* partials, int nb, DevState*
     if (code == 0 && !line_minimum(a, &x)) code = -7;
     if (writer) {
       for (int k = 0; k < 5; ++k) st->alpha[k] = a[k];
-      if (code) st->done = code;
-      else st->x = x;
+      st->line_code = code;
+      if (!code) st->x = x;
     }
     xs = x;
     found = code == 0;
@@ -782,7 +784,7 @@ __device__ __forceinline__ bool line_x(const double* partials, int nb, DevState*
 __global__ __launch_bounds__(NT) void k_line_final(const double* partials, int nb, DevState* st) {
   if (st->done) return;
   double x;
-  line_x(partials, nb, st, true, &x);
+  if (!line_x(partials, nb, st, true, &x) && threadIdx.x == 0) st->done = st->line_code;
 }
 
 // ---- updates (Eq. 16 and the footnote of Sec. 2.3) ----------------------------------------------
@@ -1133,6 +1135,10 @@ __global__ __launch_bounds__(NT) void k_update_split_line(T* C, const unsigned s
 __device__ __forceinline__ void f_update_final(const double* partials, int nb, int M, DevState* st,
                                double* trace) {
   if (st->done) return;
+  if (st->line_code) {  // the line minimum of the launch before found none: nothing was updated
+    if (threadIdx.x == 0) st->done = st->line_code;
+    return;
+  }
   __shared__ double sh[SH_SUMS];
   double s3[3];
   sum_partials_all<3>(partials, nb, sh, s3);
@@ -1213,7 +1219,7 @@ __global__ void g_line_final(const SysDev* sys) {
   const SysDev& d = sys[blockIdx.y];
   if (d.st->done) return;
   double x;
-  line_x(d.partials, GROUP_BLOCKS, d.st, true, &x);
+  if (!line_x(d.partials, GROUP_BLOCKS, d.st, true, &x) && threadIdx.x == 0) d.st->done = d.st->line_code;
 }
 template <typename T>
 __device__ __forceinline__ void g_update_mn_t(const SysDev& d) {
