@@ -141,7 +141,7 @@ struct omm_ctx {
   double p_residual = -1.0;   // probe residual of the last preconditioner inverse
   std::vector<int> ck_iter;   // FP64-exact energies of the mixed scheme: (line search, E)
   std::vector<double> ck_E;
-  int phase_k = 0;            // line searches launched in the active phase
+  int phase_k = 0;            // line searches launched in the active phase (at the start of a call: done)
   int trace_off = 0;          // offset of the active phase in the energy trace
   int iters_before = 0;       // line searches of earlier phases of the last minimize call
   // hipGraphs of two line searches (replayed after the first two of a phase), kept while nothing they
@@ -1142,6 +1142,9 @@ int phase_iterate(omm_ctx* c, Work<T>& w, int compute, const T* Hs, const T* S, 
   h->done = 0;
   h->tol = tol;
   h->max_iter = h->iter + count;
+  // line searches launched after the stop of an earlier call did nothing: the next one follows the last
+  // that ran (its parity picks the buffers of the previous gradient and the slot of <PG, G>)
+  c->phase_k = h->iter;
   TRY(ensure_trace(c, c->trace_off + h->max_iter + 2));
   HIPCHK(c, hipMemcpyAsync(c->st, h, sizeof(DevState), hipMemcpyHostToDevice, c->stream));
   double* trace = c->trace + c->trace_off;
