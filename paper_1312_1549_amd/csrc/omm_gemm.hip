@@ -328,6 +328,8 @@ hipError_t gemm_launch(const GemmDesc& d, const GemmOp* ops, int nops, const int
   if (nops < 1 || nops > 4) return hipErrorInvalidValue;
   bool tri = false;
   for (int i = 0; i < nops; ++i) {
+    // the small tiles store the rotated rows of C alone
+    if (ops[i].pair_rows && ops[i].Chi && tile_direct(d.tile)) return hipErrorInvalidValue;
     if (!ops[i].tri) continue;
     if (ops[i].M != ops[i].N || ops[i].Chi || ops[i].kptr) return hipErrorInvalidValue;
     tri |= ops[i].tri == 1;

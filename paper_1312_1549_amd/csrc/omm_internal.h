@@ -75,7 +75,7 @@ struct GemmOp {
   int kcut;
   // Paired result (real embedding of a complex product, N = 2 h columns, pair_rows = M rows
   // computed; 0: none): row M + r is the pair rotation [-Im z, Re z] of row r = [Re z, Im z], stored
-  // with it (also in the planes).
+  // with it (also in the planes, which the small tiles refuse).
   int pair_rows;
 };
 // A(m, k) = 0 for k > m; B(n, k) = 0 for k > n; B(n, k) = 0 for k < n.
