@@ -77,3 +77,40 @@ def test_device_inputs_are_checked_and_kept(api, n):
     assert np.max(np.abs(solver.preconditioner() - inv)) <= 1e4 * n * np.finfo(float).eps * np.abs(inv).max() * np.linalg.cond(S + T2 / 5.0)
     solver.set_HS(dev(H), dev(S), None)
     assert solver.minimize(C0, eta=2.0, tau=0.0, tol=0.0, max_iter=2) in (0, 1)
+
+
+@pytest.mark.parametrize("n", [1, 33, 65])
+def test_what_new_device_inputs_keep_and_drop(api, n):
+    """A new H alone keeps the preconditioner (it can be read before the next minimization); a new S, a new T
+    or a dropped T drops it. Without T the results are those of a solver that never had one, and a
+    finite tau is refused."""
+    torch, OMM, OMMError = api
+    print(f"[gpu-case] kept and dropped n={n}", flush=True)
+    H, S, T = (_spd(n, k) for k in range(3))
+    dev = lambda A: torch.from_numpy(A.copy()).cuda()  # noqa: E731
+    C0 = np.full((1, n), 1e-2)
+    solver = OMM(n, 1, precision="fp64")
+    solver.set_HS(dev(H), dev(S), dev(T))
+    solver.minimize(C0, eta=2.0, tau=5.0, tol=0.0, max_iter=2)
+    P0 = solver.preconditioner()
+    solver.set_HS(dev(H + np.eye(n)), dev(S), dev(T))
+    assert np.array_equal(solver.preconditioner(), P0)
+    dS, dT = S.copy(), T.copy()
+    dS[n - 1, n - 1] = np.nextafter(S[n - 1, n - 1], 2.0)
+    dT[0, 0] = np.nextafter(T[0, 0], 2.0)
+    for args in ((H, dS, T), (H, S, dT), (H, S, None)):
+        solver.set_HS(dev(H), dev(S), dev(T))
+        solver.minimize(C0, eta=2.0, tau=5.0, tol=0.0, max_iter=2)
+        assert np.array_equal(solver.preconditioner(), P0)
+        solver.set_HS(*(None if A is None else dev(A) for A in args))
+        with pytest.raises(OMMError, match="OMM_E_STATE"):
+            solver.preconditioner()
+    # (H, S, None) is in: tau needs T
+    with pytest.raises(OMMError, match="OMM_E_ARG"):
+        solver.minimize(C0, eta=2.0, tau=5.0, tol=0.0, max_iter=2)
+    fresh = OMM(n, 1, precision="fp64")
+    fresh.set_HS(dev(H), dev(S), None)
+    for o in (solver, fresh):
+        o.minimize(C0, eta=2.0, tau=np.inf, tol=0.0, max_iter=3)
+    assert np.array_equal(solver.energy_trace(), fresh.energy_trace())
+    assert np.array_equal(solver.get_C(), fresh.get_C())
