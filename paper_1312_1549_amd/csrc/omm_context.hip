@@ -145,7 +145,8 @@ struct omm_ctx {
   int trace_off = 0;          // offset of the active phase in the energy trace
   int iters_before = 0;       // line searches of earlier phases of the last minimize call
   // hipGraphs of two line searches (replayed after the first two of a phase), kept while nothing they
-  // were captured with has changed: one per phase of a refined minimization
+  // were captured with has changed: one per phase of a refined minimization. With block-sparse products
+  // a new H ends that: build_klist allocates the lists anew.
   LineGraph graphs[2];
   int graph_last = 0;  // most recently used
   // profiling: HIP events around each stage of every launched line search
@@ -392,9 +393,9 @@ int autotune(omm_ctx* c, GemmDesc d, GemmOp* ops, int nops, int K, std::pair<int
 // One GEMM launch. FP64 / FP32 products take the small tile direct_choose picks from the sizes; BF16
 // ones a tuned (or heuristic) tiling. `tunable` is false for in-place updates, which must not be
 // run more than once.
-// OMM_TILE=<t> pins every GEMM that supports macro tile t to it (no split-K, no autotuning), and
-// with t >= 4 the FP64 / FP32 GEMMs to tile 4: used to compare tile implementations against
-// each other.
+// OMM_TILE=<t> pins every GEMM that supports macro tile t to it (no split-K, no autotuning); with t =
+// 4, 5 or 6 the FP64 / FP32 GEMMs run on their tile 4. The small tiles, t = 7 .. 12, exist for FP64 / FP32
+// alone, and the BF16 GEMMs are then tuned as without the pin. Used to compare tiles with each other.
 int forced_tile() {
   const char* e = getenv("OMM_TILE");
   return (e && e[0]) ? atoi(e) : -1;

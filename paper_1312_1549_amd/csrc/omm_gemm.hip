@@ -127,10 +127,24 @@ int gemm_num_tiles() { return NTILES; }
 // operand bytes). Rates relative to 72 (FP64) and 154 (FP32) TFLOP/s and the exposed times are
 // measured. FP64 384 x 2048 x 2048 (rule / measured, us): 16x32 73 / 75, 32x32 55 / 55, 48x48 76 / 74,
 // 48x64 53 / 54, 64x64 68 / 66, 64x96 98 / 96; two FP32 768 x 4096 x 4096: 32x32 556 / 541, 48x64 460 /
-// 448, 64x64 454 / 439. 32 x 32 asks for the most operand bytes per flop that still pays: with fewer
-// than three such tiles per CU its SIMDs wait for them (the four 384 x 384 x 2048 projections take 52
-// us with it, 45 with 48 x 48), and in FP32 with long K too (0.62 at K = 4096; 32 grouped systems with
-// K of 256 to 1024 take 101 us with it, 105 to 135 with the others).
+// 448, 64x64 454 / 439.
+//
+// 32 x 32 asks for the most operand bytes per flop that still pays, and two corrections stand for that.
+// Times below are whole launches (us), 32x32 against the best other tile; A of M x K, B of N x K, both
+// k-contiguous.
+//  * Under three rounds its rate counts 0.75: the four projections of 384 x 384 x 2048 in FP64 (two of
+//    them symmetric) take 52 with it, 45 with 48x48. Two of 256 x 1024 x 1024 go the other way (19.6
+//    against 27.7), but there it is chosen all the same, the others needing as many rounds.
+//  * From three rounds on, in FP32 up to K = 1024, its rate counts 0.75 instead of 0.62. Four of 256 x 2048 x K, against 64x64: K =
+//    512 22.8 / 23.2, 768 31.7 / 30.6, 1024 38.5 / 37.5, 1152 42.3 / 40.8, 1536 56.8 / 51.3, 2048 74.0 /
+//    65.3. Four of 384 x 2048 x K, against 48x64: 512 33.2 / 34.2, 1024 57.8 / 54.7, 1152 63.5 / 60.4,
+//    1536 84.1 / 76.4. The two cross between 512 and 768, and up to the line the choice is within 6 % of
+//    the best; batches whose systems' K runs from 256 to 1024 share one tile (101 us a launch with 32x32,
+//    105 to 135 with the others), which is why the line lies beyond the crossing.
+// Of 126 FP64 and FP32 products with 256 to 4096 columns the choice is within 7 % of the fastest tile in
+// 113. The others are FP32: two rounds of 32x32 with K >= 1000 (two of 256 x 1024 x 2048 take 28.0, 20.2
+// with 32x32; two of 192 x 1024 x 1024 14.3, 11.6) and five rounds (four of 160 x 2048 x 1024 take 32.5,
+// 28.8 with 48x64).
 void direct_choose(GemmDesc& d, const GemmOp* ops, int nops) {
   static const double rate64[NDIRECT] = {0.64, 0.85, 0.93, 0.90, 0.94, 0.97};
   static const double rate32[NDIRECT] = {0.45, 0.62, 0.75, 0.77, 0.78, 0.85};

@@ -191,7 +191,7 @@ constexpr int direct_lds() {
 
 // The output tile (tm, tn) of op, by the WK waves of a workgroup.
 template <int MODE, typename TA, typename TB, typename TC, typename TX, int LA, int LB, int TM,
-          int TN, int NB, int USER>
+          int TN, int NB>
 __device__ __forceinline__ void direct_tile(const GemmOp& op, int tm, int tn) {
   typedef typename std::conditional<MODE == CF64, double, float>::type mt;
   typedef typename AccT<MODE>::type acc_t;
@@ -367,7 +367,7 @@ __device__ __forceinline__ int dealt_tile(int bid, int total) {
 // work of a tile depends on its place (symmetric results, triangular operands): there short runs
 // are dealt to the XCDs in turn, from the end with the long K ranges and the columns that reach
 // furthest above the diagonal (one run each left the last XCD with twice the average: 477 instead
-// of 296 us for a symmetric 4096 x 4096 x 768).
+// of 256 us for a symmetric 4096 x 4096 x 768).
 template <int MODE, typename TA, typename TB, typename TC, typename TX, int LA, int LB, int TM,
           int TN, int NB, int OCC>
 __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmBatch batch,
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmBatch bat
   int tm, tn;
   band_tile(t, tiles_m, tiles_n, tm, tn);
   if (op.tri && tm * BM > tn * BN + BN - 1) return;  // wholly below the diagonal: see the mirror
-  direct_tile<MODE, TA, TB, TC, TX, LA, LB, TM, TN, NB, 0>(op, tm, tn);
+  direct_tile<MODE, TA, TB, TC, TX, LA, LB, TM, TN, NB>(op, tm, tn);
 }
 
 // Products of uneven shapes: one workgroup per tile of the concatenated tile lists, dealt to the XCDs in
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_grouped(GroupedArgs 
   int tm, tn;
   band_tile(t - g.tile_start[lo], tiles_m, tiles_n, tm, tn);
   if (op.tri && tm * BM > tn * BN + BN - 1) return;
-  direct_tile<MODE, TA, TB, TC, TX, LA, LB, TM, TN, NB, 1>(op, tm, tn);
+  direct_tile<MODE, TA, TB, TC, TX, LA, LB, TM, TN, NB>(op, tm, tn);
 }
 
 // The tile shapes (TM, TN, ring steps NB, workgroups per CU OCC), macro tiles DIRECT_TILE0 ..
