@@ -189,9 +189,11 @@ constexpr int direct_lds() {
   return ring > red ? ring : red;
 }
 
-// The output tile (tm, tn) of op, by the WK waves of a workgroup.
+// The output tile (tm, tn) of op, by the WK waves of a workgroup. USER: a value for each calling kernel; where
+// both call the same instantiation, the compiler's host pass rejects the second call ("substitution
+// failure").
 template <int MODE, typename TA, typename TB, typename TC, typename TX, int LA, int LB, int TM,
-          int TN, int NB>
+          int TN, int NB, int USER>
 __device__ __forceinline__ void direct_tile(const GemmOp& op, int tm, int tn) {
   typedef typename std::conditional<MODE == CF64, double, float>::type mt;
   typedef typename AccT<MODE>::type acc_t;
@@ -388,7 +390,7 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmBatch bat
   int tm, tn;
   band_tile(t, tiles_m, tiles_n, tm, tn);
   if (op.tri && tm * BM > tn * BN + BN - 1) return;  // wholly below the diagonal: see the mirror
-  direct_tile<MODE, TA, TB, TC, TX, LA, LB, TM, TN, NB>(op, tm, tn);
+  direct_tile<MODE, TA, TB, TC, TX, LA, LB, TM, TN, NB, 0>(op, tm, tn);
 }
 
 // Products of uneven shapes: one workgroup per tile of the concatenated tile lists, dealt to the XCDs in
@@ -412,7 +414,7 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_grouped(GroupedArgs 
   int tm, tn;
   band_tile(t - g.tile_start[lo], tiles_m, tiles_n, tm, tn);
   if (op.tri && tm * BM > tn * BN + BN - 1) return;
-  direct_tile<MODE, TA, TB, TC, TX, LA, LB, TM, TN, NB>(op, tm, tn);
+  direct_tile<MODE, TA, TB, TC, TX, LA, LB, TM, TN, NB, 1>(op, tm, tn);
 }
 
 // The tile shapes (TM, TN, ring steps NB, workgroups per CU OCC), macro tiles DIRECT_TILE0 ..
