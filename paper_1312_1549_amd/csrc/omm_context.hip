@@ -58,22 +58,6 @@ constexpr int elem_type() {
 
 }  // namespace
 
-// A captured pair of line searches and everything its launches depend on: the buffers that may be
-// allocated anew or chosen per call, and the options that choose kernels. (All other buffers live as
-// long as the context.)
-struct GraphKey {
-  const void* buf[16];
-  int opt[12];
-  bool operator==(const GraphKey& o) const {
-    return std::equal(buf, buf + 16, o.buf) && std::equal(opt, opt + 12, o.opt);
-  }
-};
-struct LineGraph {
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  GraphKey key{};
-};
-
 struct omm_ctx {
   int64_t N = 0, M = 0;
   // complex Hermitian problem of Nc orbitals, Mc Wannier functions held as its exact real
@@ -144,11 +128,10 @@ struct omm_ctx {
   int phase_k = 0;            // line searches launched in the active phase (at the start of a call: done)
   int trace_off = 0;          // offset of the active phase in the energy trace
   int iters_before = 0;       // line searches of earlier phases of the last minimize call
-  // hipGraphs of two line searches (replayed after the first two of a phase), kept while nothing they
-  // were captured with has changed: one per phase of a refined minimization. With block-sparse products
-  // a new H ends that: build_klist allocates the lists anew.
-  LineGraph graphs[2];
-  int graph_last = 0;  // most recently used
+  // hipGraph of two line searches of the active phase (replayed after the first two)
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t graph_exec = nullptr;
+  int graph_parity = -1;  // phase_k & 1 at capture
   // profiling: HIP events around each stage of every launched line search
   bool prof = false;
   std::vector<hipEvent_t> ev_pool;
@@ -497,6 +480,7 @@ int ensure_inputs(omm_ctx* c) {
 // list) stays valid when neither changed: an SCF loop that updates H at a fixed geometry keeps
 // its preconditioner (Sec. 3 reuses the previous step's coefficients the same way).
 void invalidate(omm_ctx* c, bool s_or_t_changed) {
+  drop_graph(c);
   c->phase_active = false;
   c->phase_mixed64 = false;
   c->kl_valid[0] = false;
@@ -603,6 +587,7 @@ int prepare_shift(omm_ctx* c, double eta) {
     c->hs_eta = eta;
     c->hs_reduced = red;
     c->kl_valid[0] = false;
+    drop_graph(c);  // a captured graph may hold the old Hs lists
     c->hs32_valid = false;
     c->hsp_valid = false;
   }
@@ -1057,14 +1042,12 @@ int ensure_trace(omm_ctx* c, int need) {
   return OMM_OK;
 }
 
-void drop_one(LineGraph& g) {
-  if (g.exec) (void)hipGraphExecDestroy(g.exec);
-  if (g.graph) (void)hipGraphDestroy(g.graph);
-  g = LineGraph{};
-}
-
 void drop_graph(omm_ctx* c) {
-  for (LineGraph& g : c->graphs) drop_one(g);
+  if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
+  if (c->graph) (void)hipGraphDestroy(c->graph);
+  c->graph_exec = nullptr;
+  c->graph = nullptr;
+  c->graph_parity = -1;
 }
 
 bool graphs_enabled(omm_ctx* c) {
@@ -1072,29 +1055,12 @@ bool graphs_enabled(omm_ctx* c) {
   return !c->prof && !(e && e[0] == '0');
 }
 
+// Captures line searches k and k+1 (same buffers every time; only the parity of k matters). The graph is
+// the active phase's: it is not kept for the next call.
 template <typename T>
-GraphKey graph_key(const omm_ctx* c, const Work<T>& w, int compute, const T* Hs, const T* S, const T* P,
-                   int k, const double* trace) {
-  return GraphKey{{Hs, S, P, w.C, w.D, w.PGf, w.Gf, trace, c->ws, c->kl_ptr[0], c->kl_idx[0], c->kl_ptr[1],
-                   c->kl_idx[1], c->Hs_p.hi, c->S_p.hi, c->P_p.hi},
-                  {compute, (int)sizeof(T), k & 1, c->p_kind > 0, c->flavour, sparse_products(c),
-                   fuse_enabled(), pg_split_enabled(), forced_tile(), autotune_enabled(), c->mode, c->refine}};
-}
-
-// The graph of line searches k and k + 1 (same buffers every time; only the parity of k matters):
-// the kept one if it was captured with the same key, else captured anew.
-template <typename T>
-int line_graph(omm_ctx* c, Work<T>& w, int compute, const T* Hs, const T* S, const T* P, int k,
-               double* trace, LineGraph** out) {
-  GraphKey key = graph_key(c, w, compute, Hs, S, P, k, trace);
-  for (int i = 0; i < 2; ++i)
-    if (c->graphs[i].exec && c->graphs[i].key == key) {
-      c->graph_last = i;
-      *out = &c->graphs[i];
-      return OMM_OK;
-    }
-  const int slot = c->graphs[c->graph_last].exec ? 1 - c->graph_last : c->graph_last;
-  drop_one(c->graphs[slot]);
+int capture_pair(omm_ctx* c, Work<T>& w, int compute, const T* Hs, const T* S, const T* P, int k,
+                 double* trace) {
+  drop_graph(c);
   HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
   int r = line_search_iteration<T>(c, w, compute, Hs, S, P, k, trace);
   if (r == OMM_OK) r = line_search_iteration<T>(c, w, compute, Hs, S, P, k + 1, trace);
@@ -1105,12 +1071,9 @@ int line_graph(omm_ctx* c, Work<T>& w, int compute, const T* Hs, const T* S, con
     return r;
   }
   HIPCHK(c, e);
-  LineGraph& lg = c->graphs[slot];
-  lg.graph = g;
-  HIPCHK(c, hipGraphInstantiate(&lg.exec, lg.graph, nullptr, nullptr, 0));
-  lg.key = key;
-  c->graph_last = slot;
-  *out = &lg;
+  c->graph = g;
+  HIPCHK(c, hipGraphInstantiate(&c->graph_exec, c->graph, nullptr, nullptr, 0));
+  c->graph_parity = k & 1;
   return OMM_OK;
 }
 
@@ -1123,6 +1086,7 @@ int phase_begin(omm_ctx* c, Work<T>& w, int compute, const T* Hs, const T* S, do
   init.max_iter = 0;
   HIPCHK(c, hipMemcpyAsync(c->st, &init, sizeof(DevState), hipMemcpyHostToDevice, c->stream));
   TRY(ensure_trace(c, trace_off + 2));
+  drop_graph(c);
   TRY(initial_products<T>(c, w, compute, Hs, S, c->trace + trace_off));
   TRY(read_state(c));
   c->phase_active = true;
@@ -1154,14 +1118,14 @@ int phase_iterate(omm_ctx* c, Work<T>& w, int compute, const T* Hs, const T* S, 
   const int check = c->N >= 4096 ? 2 : 8;
   if (count > 0) {
     // The first two line searches of a phase run eagerly (every BF16 GEMM shape is tuned and its
-    // workspace allocated); after that pairs of line searches replay a captured graph.
+    // workspace allocated); after that pairs of line searches replay one captured graph.
     const bool graphs = graphs_enabled(c);
     int since = 0;
-    LineGraph* g = nullptr;  // pairs keep the parity, so one graph serves the whole call
     for (int k = 0; k < count;) {
       if (graphs && c->phase_k >= 2 && count - k >= 2) {
-        if (!g) TRY(line_graph<T>(c, w, compute, Hs, S, P, c->phase_k, trace, &g));
-        HIPCHK(c, hipGraphLaunch(g->exec, c->stream));
+        if (!c->graph_exec || c->graph_parity != (c->phase_k & 1))
+          TRY(capture_pair<T>(c, w, compute, Hs, S, P, c->phase_k, trace));
+        HIPCHK(c, hipGraphLaunch(c->graph_exec, c->stream));
         k += 2;
         c->phase_k += 2;
         since += 2;
