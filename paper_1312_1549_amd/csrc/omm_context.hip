@@ -1548,7 +1548,9 @@ int omm_checkpoints(omm_ctx* c, int* iters, double* energies, int cap, int* n) {
 int omm_set_stream(omm_ctx* c, void* s) {
   if (!c) return OMM_E_ARG;
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  c->stream = s ? (hipStream_t)s : c->own;
+  hipStream_t next = s ? (hipStream_t)s : c->own;
+  if (next != c->stream) drop_graph(c);  // a graph runs on the stream it was captured on
+  c->stream = next;
   return OMM_OK;
 }
 
